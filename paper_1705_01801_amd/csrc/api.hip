@@ -833,7 +833,8 @@ int lbw_modes(lbw_state_t s, int k, double* freq_out, double* power_out) {
     const int64_t T = s->t < s->t_max ? s->t : s->t_max;
     if (T < 8) return fail(LBW_EINVAL, "need at least 8 recorded rows (have %lld)", (long long)T);
     if (s->n_probes > lbw::modes_max_cols(T)) return fail(LBW_EINVAL, "too many probes for one spectrum");
-    const size_t need = lbw::modes_work_bytes(T, s->n_probes, 1);
+    const int ncols = s->n_probes;
+    const size_t need = lbw::modes_work_bytes(T, &ncols, 1);
     if (need > s->mode_work_bytes) {
         (void)hipFree(s->mode_work);
         s->mode_work = nullptr;
@@ -848,7 +849,6 @@ int lbw_modes(lbw_state_t s, int k, double* freq_out, double* power_out) {
         HIP_TRY(hipMalloc(&s->mode_out, sizeof(double) * 2 * k), "lbw_modes");
         s->mode_k = k;
     }
-    const int ncols = s->n_probes;
     HIP_TRY(lbw::launch_modes_grouped(s->trace, T, s->n_probes, &ncols, 1, k, s->mode_work, s->mode_work_bytes,
                                       s->mode_out, s->mode_out + k, s->stream),
             "lbw_modes");

@@ -628,8 +628,7 @@ int lbw_batch_modes(lbw_batch_t b, int k, double* freq_out, double* power_out) {
     }
     const int cap = lbw::modes_max_cols(T);
     if (max_group > cap) return fail(LBW_EINVAL, "too many probes in one geometry for one spectrum");
-    const int chunk_cols = (int)std::min<int64_t>(cap, b->P);
-    const size_t need = lbw::modes_work_bytes(T, chunk_cols, b->n);
+    const size_t need = lbw::modes_work_bytes(T, cols.data(), b->n);
     if (need > b->mode_work_bytes) {
         (void)hipFree(b->mode_work);
         b->mode_work = nullptr;

@@ -208,16 +208,19 @@ hipError_t launch_amplitude(const double* trace, int64_t stride, int64_t cols, i
 
 // Spectra of probe groups (consecutive trace columns, one group per
 // geometry): fills freq/power (device, groups * k each) from trace rows
-// [0, T) of row length `stride`.  Synchronises the stream per chunk.
+// [0, T) of row length `stride`, on a work space of modes_work_bytes (0: a
+// group has more columns than one spectrum takes).  Waits for the stream
+// only where the groups differ in size (their lists are copied to the device).
 int64_t modes_nfft(int64_t T);
 int modes_max_cols(int64_t T);
-size_t modes_work_bytes(int64_t T, int max_cols, int max_groups);
+size_t modes_work_bytes(int64_t T, const int* group_ncols, int groups);
 hipError_t launch_modes_grouped(const double* trace, int64_t T, int64_t stride, const int* group_ncols, int groups,
                                 int k, double* work, size_t work_bytes, double* freq, double* power, hipStream_t st);
 // The same spectrum for one group of ncols columns without allocating: the
 // work space is the library's fixed device array (kModesScratchBytes per
 // GPU; modes_scratch gives its address on the current device), columns are
-// transformed modes_static_cols(T) at a time and their power accumulated.
+// transformed modes_static_cols(T) at a time and their power added up in the
+// order of launch_modes_grouped.
 // Nothing is waited for; freq and power (k doubles each) are device memory.
 constexpr size_t kModesScratchBytes = size_t(32) << 20;
 hipError_t modes_scratch(void** ptr);
