@@ -243,7 +243,8 @@ int lbw_autotune(lbw_state_t s, int reps, double* best_us);
 
 /* Number of steps lbw_step_n captures into one HIP graph and replays
  * (0 disables graphs; default 32).  Graphs are rebuilt when the launch
- * shape changes. */
+ * shape changes.  Launches of several steps of a 2-D grid are queued
+ * directly, whatever this number is. */
 int lbw_set_graph_block(lbw_state_t s, int steps);
 
 /* Copies trace rows [t0, t1) (t1 <= recorded rows) to host memory,

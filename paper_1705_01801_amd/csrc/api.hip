@@ -28,6 +28,7 @@ struct lbw_geometry {
     GeomDev dev{};
     lbw::MarchPlan plan{};  // launch shape of the 3-D step
     lbw::MarchPlan plan2{}; // launch shape of the two-step pass, used when use2
+    lbw::Tile2Plan tile2{}; // several steps per launch of a 2-D grid
     bool use2 = false;
     int plan_version = 0;   // bumped on every change of plan
 };
@@ -41,14 +42,13 @@ struct lbw_state {
     int n_probes = 0;
     double* trace = nullptr;
     int64_t* d_probes = nullptr;
-    int64_t* d_tcount = nullptr;
+    int64_t* d_tcount = nullptr;         // step counter, two banks (one per population buffer)
     hipStream_t stream = nullptr;
     double* mode_work = nullptr;
     size_t mode_work_bytes = 0;
     double* mode_out = nullptr;  // device, 2 * mode_k
     int mode_k = 0;
-    int64_t* d_scratch_count = nullptr;  // step counter for timing launches
-    unsigned* d_done = nullptr;          // workgroups done in a two-step launch (real and timing runs)
+    int64_t* d_scratch_count = nullptr;  // step counter for timing launches (two banks)
     std::vector<int64_t> probes_host;    // probe nodes (tiles of the two-step pass hold at most a few)
     lbw::SourceEntry* d_src = nullptr;   // driven sources, imposed before every step
     int n_src = 0;
@@ -232,6 +232,7 @@ int lbw_make_geometry(const lbw_geometry_desc* desc, void* stream, lbw_geometry_
     }
     g->dev = lbw::make_geomdev(d, g->tab32, g->tab64 + 7 * g->E);
     const GeomDev& v = g->dev;
+    if (d.dim == 2) g->tile2 = lbw::make_tile2_plan(v, cus);
     if (d.dim == 3) {
         const int tx = lbw::march_tx_for(v.n0);
         g->plan = lbw::make_march_plan(v, tx, 256 / tx, 16, cus * lbw::march_blocks_per_cu(tx, 256 / tx));
@@ -483,22 +484,19 @@ int lbw_init(lbw_geometry_t g, const double* p0, float* f_a, float* f_b, const i
     s->trace = trace;
     s->stream = (hipStream_t)stream;
     s->probes_host.assign(probes, probes + n_probes);
-    hipError_t e = hipMalloc(&s->d_tcount, sizeof(int64_t));
-    if (e == hipSuccess) e = hipMalloc(&s->d_scratch_count, sizeof(int64_t));
-    if (e == hipSuccess) e = hipMalloc(&s->d_done, 2 * sizeof(unsigned));
-    if (e == hipSuccess) e = hipMemsetAsync(s->d_done, 0, 2 * sizeof(unsigned), s->stream);
+    hipError_t e = hipMalloc(&s->d_tcount, 2 * sizeof(int64_t));
+    if (e == hipSuccess) e = hipMalloc(&s->d_scratch_count, 2 * sizeof(int64_t));
     if (e == hipSuccess && n_probes > 0) e = hipMalloc(&s->d_probes, sizeof(int64_t) * n_probes);
     if (e == hipSuccess && n_probes > 0)
         e = hipMemcpyAsync(s->d_probes, probes, sizeof(int64_t) * n_probes, hipMemcpyHostToDevice, s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->d_tcount, 0, sizeof(int64_t), s->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s->d_scratch_count, 0, sizeof(int64_t), s->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(s->d_tcount, 0, 2 * sizeof(int64_t), s->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(s->d_scratch_count, 0, 2 * sizeof(int64_t), s->stream);
     if (e == hipSuccess && s->stream != g->stream) e = hipStreamSynchronize(g->stream);
     if (e == hipSuccess) e = lbw::launch_init(g->dev, p0, f_a, s->stream);
     if (e == hipSuccess && n_probes > 0) e = hipStreamSynchronize(s->stream);  // host probe list may go away
     if (e != hipSuccess) {
         (void)hipFree(s->d_tcount);
         (void)hipFree(s->d_scratch_count);
-        (void)hipFree(s->d_done);
         (void)hipFree(s->d_probes);
         delete s;
         return hip_fail(e, "lbw_init");
@@ -509,9 +507,15 @@ int lbw_init(lbw_geometry_t g, const double* p0, float* f_a, float* f_b, const i
 
 namespace {
 
-hipError_t launch_one(lbw_state* s, const lbw::ProbeArgs& pr, int from, hipStream_t st) {
+// The state's probes and counter banks for a launch that reads buffer `from`.
+lbw::ProbeArgs probe_args(const lbw_state* s, int from) {
+    return lbw::ProbeArgs{s->d_probes, s->n_probes, s->trace, s->t_max, s->d_tcount + from, s->d_tcount + (1 - from)};
+}
+
+hipError_t launch_one(lbw_state* s, int from, hipStream_t st) {
+    const lbw::ProbeArgs pr = probe_args(s, from);
     if (s->n_src > 0) {
-        const hipError_t e = lbw::launch_sources(s->d_src, s->n_src, s->d_tcount, s->f[from], st);
+        const hipError_t e = lbw::launch_sources(s->d_src, s->n_src, pr.tin, s->f[from], st);
         if (e != hipSuccess) return e;
     }
     if (s->g->general)
@@ -555,8 +559,16 @@ bool two_step_ok(const lbw_state* s) {
 }
 
 hipError_t launch_two(lbw_state* s, int from, hipStream_t st) {
-    lbw::ProbeArgs pr{s->d_probes, s->n_probes, s->trace, s->t_max, s->d_tcount, s->d_done};
-    return lbw::launch_step_march2(s->g->dev, pr, s->g->plan2, s->f[from], s->f[1 - from], st);
+    return lbw::launch_step_march2(s->g->dev, probe_args(s, from), s->g->plan2, s->f[from], s->f[1 - from], st);
+}
+
+// Several steps per launch of a 2-D grid: where the tiling applies, without
+// driven sources (they are imposed between steps) and with no more probes
+// than one tile records.
+bool tile2_ok(const lbw_state* s) {
+    const lbw_geometry* g = s->g;
+    return g->dev.dim == 2 && g->tile2.rows > 0 && s->n_src == 0 &&
+           (s->t >= s->t_max || s->n_probes <= lbw::tile2_probes());
 }
 
 void drop_graphs(lbw_state* s) {
@@ -573,7 +585,6 @@ hipError_t build_graph(lbw_state* s, int from, bool two) {
     hipStream_t cap = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
     if (e != hipSuccess) return e;
-    lbw::ProbeArgs pr{s->d_probes, s->n_probes, s->trace, s->t_max, s->d_tcount};
     hipGraph_t graph = nullptr;
     e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
@@ -581,7 +592,7 @@ hipError_t build_graph(lbw_state* s, int from, bool two) {
         hipError_t le = hipSuccess;
         const int launches = two ? s->graph_block / 2 : s->graph_block;
         for (int i = 0; i < launches && le == hipSuccess; ++i) {
-            le = two ? launch_two(s, cur, cap) : launch_one(s, pr, cur, cap);
+            le = two ? launch_two(s, cur, cap) : launch_one(s, cur, cap);
             cur ^= 1;
         }
         e = hipStreamEndCapture(cap, &graph);
@@ -598,7 +609,20 @@ hipError_t build_graph(lbw_state* s, int from, bool two) {
 int lbw_step_n(lbw_state_t s, int64_t n) {
     if (!s) return fail(LBW_EINVAL, "state is NULL");
     if (n < 0) return fail(LBW_EINVAL, "negative step count");
-    lbw::ProbeArgs pr{s->d_probes, s->n_probes, s->trace, s->t_max, s->d_tcount, s->d_done};
+    if (n > 1 && tile2_ok(s)) {
+        // a launch of several steps takes longer than queueing the next one,
+        // so these are launched directly, not through captured blocks
+        while (n > 0) {
+            const int k = (int)std::min<int64_t>(n, s->g->tile2.k);
+            HIP_TRY(lbw::launch_step_tile2(s->g->dev, probe_args(s, s->cur), s->g->tile2, k, s->f[s->cur],
+                                           s->f[1 - s->cur], s->stream),
+                    "lbw_step_n");
+            s->cur ^= 1;
+            s->t += k;
+            n -= k;
+        }
+        return LBW_OK;
+    }
     const bool two = two_step_ok(s);
     // steps per captured block: even for two-step launches
     const int K = two ? s->graph_block & ~1 : s->graph_block;
@@ -624,7 +648,7 @@ int lbw_step_n(lbw_state_t s, int64_t n) {
         n -= 2;
     }
     for (int64_t i = 0; i < n; ++i) {
-        HIP_TRY(launch_one(s, pr, s->cur, s->stream), "lbw_step_n");
+        HIP_TRY(launch_one(s, s->cur, s->stream), "lbw_step_n");
         s->cur ^= 1;
         s->t += 1;
     }
@@ -667,9 +691,16 @@ int lbw_autotune(lbw_state_t s, int reps, double* best_us) {
     if (err == hipSuccess && s->n_probes > 0)
         err = hipMalloc((void**)&ptrace, sizeof(double) * (size_t)trows * (size_t)s->n_probes);
     const int np = ptrace ? s->n_probes : 0;
-    lbw::ProbeArgs pr{np ? s->d_probes : nullptr, np, ptrace, np ? trows : 0, s->d_scratch_count};
+    lbw::ProbeArgs pr{np ? s->d_probes : nullptr, np, ptrace, np ? trows : 0, nullptr, nullptr};
+    int bank = 0;  // every launch reads the counter bank that the one before wrote
+    auto next_pr = [&]() -> const lbw::ProbeArgs& {
+        pr.tin = s->d_scratch_count + bank;
+        pr.tout = s->d_scratch_count + (1 - bank);
+        bank ^= 1;
+        return pr;
+    };
     auto restart = [&]() {
-        if (err == hipSuccess) err = hipMemsetAsync(s->d_scratch_count, 0, sizeof(int64_t), s->stream);
+        if (err == hipSuccess) err = hipMemsetAsync(s->d_scratch_count, 0, 2 * sizeof(int64_t), s->stream);
     };
     const lbw::MarchPlan keep = g->plan;
     lbw::MarchPlan best = keep;
@@ -682,10 +713,10 @@ int lbw_autotune(lbw_state_t s, int reps, double* best_us) {
         int w = 0;
         auto run = [&](int n) {
             for (int r = 0; r < n && err == hipSuccess; ++r, w ^= 1)
-                err = lbw::launch_step_march(g->dev, pr, p, bufs[w], bufs[w ^ 1], s->stream);
+                err = lbw::launch_step_march(g->dev, next_pr(), p, bufs[w], bufs[w ^ 1], s->stream);
         };
         restart();
-        if (err == hipSuccess) err = lbw::launch_step_march(g->dev, pr, p, s->f[s->cur], other, s->stream);
+        if (err == hipSuccess) err = lbw::launch_step_march(g->dev, next_pr(), p, s->f[s->cur], other, s->stream);
         run(2);
         if (err == hipSuccess) err = hipEventRecord(e0, s->stream);
         run(count);
@@ -697,17 +728,15 @@ int lbw_autotune(lbw_state_t s, int reps, double* best_us) {
     };
     // two time steps per launch: timed per step (reps launches = 2 reps
     // steps), on the same ping-pong buffers with the timing step counter
-    // and its own completion counter
-    const lbw::ProbeArgs pr2{pr.nodes, pr.n, pr.trace, pr.t_max, s->d_scratch_count, s->d_done + 1};
     auto time2 = [&](const lbw::MarchPlan& p, int count) -> float {
         float* bufs[2] = {other, tmp};
         int w = 0;
         auto run = [&](int n) {
             for (int r = 0; r < n && err == hipSuccess; ++r, w ^= 1)
-                err = lbw::launch_step_march2(g->dev, pr2, p, bufs[w], bufs[w ^ 1], s->stream);
+                err = lbw::launch_step_march2(g->dev, next_pr(), p, bufs[w], bufs[w ^ 1], s->stream);
         };
         restart();
-        if (err == hipSuccess) err = lbw::launch_step_march2(g->dev, pr2, p, s->f[s->cur], other, s->stream);
+        if (err == hipSuccess) err = lbw::launch_step_march2(g->dev, next_pr(), p, s->f[s->cur], other, s->stream);
         run(2);
         if (err == hipSuccess) err = hipEventRecord(e0, s->stream);
         run(count);
@@ -962,7 +991,6 @@ int lbw_free_state(lbw_state_t s) {
     (void)hipStreamSynchronize(s->stream);
     drop_graphs(s);
     (void)hipFree(s->d_scratch_count);
-    (void)hipFree(s->d_done);
     (void)hipFree(s->d_tcount);
     (void)hipFree(s->d_probes);
     (void)hipFree(s->d_src);

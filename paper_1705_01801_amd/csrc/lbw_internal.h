@@ -72,10 +72,24 @@ struct ProbeArgs {
     int n;
     double* trace;         // device, t_max * n
     int64_t t_max;
-    int64_t* tcount;       // device step counter
-    unsigned* tdone;       // device, workgroups finished in the current two-step launch (0 between launches)
+    // device step counter in two banks, one per population buffer: a launch
+    // reads the bank of the buffer it reads and writes that of the buffer it
+    // writes, so no block of it reads a counter that another block changes
+    const int64_t* tin;
+    int64_t* tout;
 };
 hipError_t launch_step(const GeomDev& g, const ProbeArgs& pr, const float* fin, float* fout, hipStream_t st);
+// Up to plan.k time steps of a 2-D grid per launch (step_tile2d.hip).
+struct Tile2Plan {
+    int rows;       // rows of a wave's strip (0: this path does not apply)
+    int waves;      // strips per workgroup
+    int ntx, nty;   // tiles along axes 0 and 1
+    int k;          // steps per launch
+};
+Tile2Plan make_tile2_plan(const GeomDev& g, int cus);
+int tile2_probes();  // probes a tile records at most
+hipError_t launch_step_tile2(const GeomDev& g, const ProbeArgs& pr, const Tile2Plan& plan, int steps,
+                             const float* fin, float* fout, hipStream_t st);
 // One step of a geometry given by its metric (3-D, per-node coefficients),
 // z-marching tiles (plan.tx x plan.ty = 256 threads, plan.lz planes, one
 // workgroup per tile); probes recorded as in the other step kernels.
@@ -106,8 +120,7 @@ hipError_t launch_step_march(const GeomDev& g, const ProbeArgs& pr, const MarchP
 // threads own ty whole axis-0 rows (n0 <= tx, axis 0 walled) over chunks of
 // lz planes, or (lz 0) over balanced shares of all (row tile, plane) pairs;
 // plan.ntx is 1.  Shapes: 96 x 6 and 128 x 4 (768 threads).
-// The step counter advances by two per launch (needs pr.tdone); the probes
-// of both times are recorded, at most march2_tile_probes() per tile.
+// The step counter advances by two per launch; the probes of both times are recorded, at most march2_tile_probes() per tile.
 bool march2_shape_ok(int tx, int ty);
 // Balanced two-step plans (lz 0): workgroup b of `blocks` (a multiple of 8)
 // takes the pairs [a, e) of the `total` (row tile, plane) pairs, row tile

@@ -96,6 +96,26 @@ __device__ inline void bload7p(__amdgpu_buffer_rsrc_t r, uint32_t N4, bool on, u
             __builtin_amdgcn_raw_buffer_load_b32(r, (int)(base + (uint32_t)l * N4), 0, NTL ? kNontemporal : 0));
 }
 
+// Probes of time t read from the input buffer by one workgroup (trace[t][p]
+// = sum_l f_l(node_p) / sqrt(g)), and the step counter advanced by `steps`.
+// The values do not wait for t: a probe costs the node list, then the
+// populations and sqrt(g) together (one workgroup's serial chain was most of
+// a small grid's launch).
+template <int Q>
+__device__ inline void record_probes(const GeomDev& g, const ProbeArgs& pr, int steps, const float* __restrict__ fin) {
+    const int64_t t = *pr.tin;
+    for (int p = threadIdx.x; p < pr.n; p += blockDim.x) {
+        const uint32_t node = (uint32_t)pr.nodes[p], N = (uint32_t)g.N;
+        const uint32_t n0 = (uint32_t)g.n0;
+        const double sg = g.sqrtg[g.sg_node ? node : node % n0 + n0 * (node / (n0 * (uint32_t)g.n1))];
+        double s = 0.0;
+#pragma unroll
+        for (int l = 0; l < Q; ++l) s += (double)fin[(uint32_t)l * N + node];
+        if (t >= 0 && t < pr.t_max) pr.trace[t * pr.n + p] = s / sg;
+    }
+    if (threadIdx.x == 0) *pr.tout = t + steps;
+}
+
 // value beyond a wall: mirrored, odd for fixed walls
 __device__ inline float ghost(int wall, float v) { return wall == LBW_BC_FIXED ? -v : v; }
 
@@ -103,6 +123,24 @@ __device__ inline float ghost(int wall, float v) { return wall == LBW_BC_FIXED ?
 // bounce-back D f*_l, free f*_{lbar} (the node's own), fixed -f*_l
 __device__ inline float bounce(int wall, float damp, float out_l, float own_lb) {
     return wall == LBW_BC_BOUNCEBACK ? damp * out_l : (wall == LBW_BC_FREE ? own_lb : -out_l);
+}
+
+// Collision at one node of a 2-D grid, the rule of collide() below: a00p ..
+// a11m are the products A^{00} = c^2 Mhat00 S and A^{11} = c^2 Mhat11 S of
+// the four neighbours (the node's own, mirrored, beyond a wall), hG0 the
+// node's c^2 Gamh0 / 2.  The roundings are fixed here, so both 2-D kernels
+// give the same bits.
+__device__ __forceinline__ void collide_2d(const float (&f)[5], float S, float a00p, float a00m, float a11p,
+                                           float a11m, float hG0, float c2, float two_w0, float (&fs)[5]) {
+#pragma clang fp contract(off)
+    const float K0 = __builtin_fmaf(-0.25f, a00p - a00m, __builtin_fmaf(-hG0, S, f[1] - f[2]));
+    const float K1 = __builtin_fmaf(-0.25f, a11p - a11m, f[3] - f[4]);
+    const float cs = c2 * S;
+    fs[0] = __builtin_fmaf(two_w0, S, -f[0]);
+    fs[1] = __builtin_fmaf(c2, S, K0) - f[1];
+    fs[2] = __builtin_fmaf(c2, S, -K0) - f[2];
+    fs[3] = (K1 + cs) - f[3];
+    fs[4] = (cs - K1) - f[4];
 }
 
 // The links of one node: neighbour coordinate along each axis and direction

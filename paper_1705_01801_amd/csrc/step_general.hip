@@ -24,7 +24,7 @@
 // coefficients loaded one plane ahead by the first 2 TX + 2 TY threads.  Workgroup 0 records
 // the probes of time t before any population is written and advances the
 // step counter.
-#include "lbw_internal.h"
+#include "march_common.h"
 
 namespace lbw {
 namespace {
@@ -87,20 +87,7 @@ __global__ __launch_bounds__(NT) void general_march_kernel(GeomDev g, ProbeArgs 
     // LDS products per slot: 0 A^{00}, 1 A^{11}, 2 A^{01}, 3 A^{02}, 4 A^{12}
     __shared__ float sA[2][5][SLOTS + 1];  // + a sink slot
 
-    if (blockIdx.x == 0) {
-        const int64_t t = *(volatile const int64_t*)pr.tcount;
-        __syncthreads();
-        if (t >= 0 && t < pr.t_max) {
-            for (int p = threadIdx.x; p < pr.n; p += blockDim.x) {
-                const int64_t node = pr.nodes[p];
-                double s = 0.0;
-                for (int l = 0; l < 7; ++l) s += (double)fin[l * g.N + node];
-                pr.trace[t * pr.n + p] = s / g.sqrtg[sg_index(g, node)];
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) *(volatile int64_t*)pr.tcount = t + 1;
-    }
+    if (blockIdx.x == 0) march::record_probes<7>(g, pr, 1, fin);
 
     const int n0 = g.n0, n1 = g.n1, n2 = g.n2;
     const int64_t N = g.N, plane = (int64_t)n0 * n1;

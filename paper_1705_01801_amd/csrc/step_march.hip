@@ -85,21 +85,6 @@ constexpr int lds_s() {
     return RT ? 4 * NT + 8 : (NT / TX + 2) * (TX + 2) + 1;
 }
 
-__device__ void probe_block(const GeomDev& g, const ProbeArgs& pr, const float* __restrict__ fin) {
-    const int64_t t = *(volatile const int64_t*)pr.tcount;
-    __syncthreads();
-    if (t >= 0 && t < pr.t_max) {
-        for (int p = threadIdx.x; p < pr.n; p += blockDim.x) {
-            const int64_t node = pr.nodes[p];
-            double s = 0.0;
-            for (int l = 0; l < 7; ++l) s += (double)fin[l * g.N + node];
-            pr.trace[t * pr.n + p] = s / g.sqrtg[sg_index(g, node)];
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) *(volatile int64_t*)pr.tcount = t + 1;
-}
-
 // One tile of one geometry: columns [x0, x0 + TX) x [y0, y0 + TY), planes
 // [z0, z0 + lz).  fin/fout point at the geometry's own population block.
 // RT: the tile is g.rtx x g.rty columns instead (at most NT of them, with
@@ -404,7 +389,7 @@ __global__ __launch_bounds__(NT) void step_march_kernel(GeomDev g, ProbeArgs pr,
     __shared__ float sS[2][lds_s<TX, NT, false>()];
     __shared__ float4 sElo[3][TX + 3];
     __shared__ float4 sEhi[3][TX + 3];
-    if (blockIdx.x == 0) probe_block(g, pr, fin);
+    if (blockIdx.x == 0) record_probes<7>(g, pr, 1, fin);
     TileGeom tg;
     tg.n0 = g.n0;
     tg.n1 = g.n1;

@@ -28,9 +28,7 @@
 //    order as a one-step launch would, so the result is that of two single
 //    steps, bit for bit;
 //  - probes: block 0 records time t from the input; the thread that owns a
-//    probe node records time t+1 from the state it assembled; the last
-//    workgroup to finish advances the step counter by two, so graph replays
-//    need no host input.
+//    probe node records time t+1 from the state it assembled.
 // Chunks along axis 2 are extended by two planes of step A either side (the
 // state at t+1 of planes z0-1 and z1 is needed), which is the price of the
 // chunking besides the two halo rows.
@@ -464,16 +462,8 @@ __global__ __launch_bounds__(TX * (TY + 2)) void step_march2_kernel(GeomDev g, P
                                                                     const float* __restrict__ fin,
                                                                     float* __restrict__ fout) {
     __shared__ M2Lds<TX, TY> L;
-    const int64_t t = *(volatile const int64_t*)pr.tcount;
-    if (blockIdx.x == 0 && t >= 0 && t < pr.t_max) {
-        // time t from the input
-        for (int p = threadIdx.x; p < pr.n; p += blockDim.x) {
-            const int64_t node = pr.nodes[p];
-            double s = 0.0;
-            for (int l = 0; l < 7; ++l) s += (double)fin[l * g.N + node];
-            pr.trace[t * pr.n + p] = s / g.sqrtg[sg_index(g, node)];
-        }
-    }
+    const int64_t t = *pr.tin;
+    if (blockIdx.x == 0) record_probes<7>(g, pr, 2, fin);  // time t, from the input
     if (plan.lz > 0) {
         // tiles of chunk_z planes, XCD-contiguous ranges of the tile list
         const int xcd = blockIdx.x % kXcds;
@@ -494,18 +484,6 @@ __global__ __launch_bounds__(TX * (TY + 2)) void step_march2_kernel(GeomDev g, P
             const int z1 = (int)min((int64_t)g.n2, (int64_t)z0 + (e - a));
             march2_tile<TX, TY, PERY, PERZ>(g, pr, t, ty, z0, z1, fin, fout, L);
             a += z1 - z0;
-        }
-    }
-    // the last workgroup to finish advances the step counter by two (every
-    // workgroup read it before counting itself done)
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        const unsigned prev = atomicAdd(pr.tdone, 1u);
-        if (prev == gridDim.x - 1) {
-            *(volatile int64_t*)pr.tcount = t + 2;
-            *(volatile unsigned*)pr.tdone = 0u;
-            __threadfence();
         }
     }
 }
@@ -571,7 +549,7 @@ void launch2_of(bool pery, bool perz, dim3 grid, dim3 block, hipStream_t st, con
 
 hipError_t launch_step_march2(const GeomDev& g, const ProbeArgs& pr, const MarchPlan& plan, const float* fin,
                               float* fout, hipStream_t st) {
-    if (!march2_shape_ok(plan.tx, plan.ty) || !march2_fits(g, plan.tx) || !pr.tdone) return hipErrorInvalidValue;
+    if (!march2_shape_ok(plan.tx, plan.ty) || !march2_fits(g, plan.tx)) return hipErrorInvalidValue;
     const dim3 grid(plan.blocks), block(plan.tx * (plan.ty + 2));
     const bool pery = g.bc_lo[1] == LBW_BC_PERIODIC, perz = g.bc_lo[2] == LBW_BC_PERIODIC;
     if (plan.tx == 96)
