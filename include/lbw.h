@@ -163,7 +163,9 @@ int lbw_stability_bound(lbw_geometry_t g, double* c_max);
  * to 1024 threads; rows of up to 96 or 128 nodes in one tile); chunk_z >= 1
  * planes per tile along axis 2; blocks:
  * persistent grid size, rounded down to a multiple of 8 (0 = one full wave
- * of resident workgroups).  Used by lbw_autotune and by tests.
+ * of resident workgroups).  A new geometry takes a shape by a rule on its
+ * grid (and lbw_set_step2_config's launches where the rule expects them to
+ * be faster).  Used by lbw_autotune and by tests.
  * A geometry given by its metric (LBW_GENERAL) has its own kernel: tile
  * 32 x 8, 64 x 4 or 64 x 8, any chunk_z, blocks 0 (one workgroup per tile;
  * default 64 x 8 when n0 > 32, else 32 x 8, chunk 16).

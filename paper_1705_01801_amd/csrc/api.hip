@@ -58,6 +58,8 @@ struct lbw_state {
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     int graph_version = -1;
     bool graph_two = false;  // the captured blocks are two-step launches
+    int fit_version = -1;    // plan version that probes_fit was worked out for
+    bool probes_fit = false; // no tile of the two-step pass holds more probes than it records
 };
 
 namespace {
@@ -234,14 +236,14 @@ int lbw_make_geometry(const lbw_geometry_desc* desc, void* stream, lbw_geometry_
     const GeomDev& v = g->dev;
     if (d.dim == 2) g->tile2 = lbw::make_tile2_plan(v, cus);
     if (d.dim == 3) {
-        const int tx = lbw::march_tx_for(v.n0);
-        g->plan = lbw::make_march_plan(v, tx, 256 / tx, 16, cus * lbw::march_blocks_per_cu(tx, 256 / tx));
+        lbw::choose_march_plans(v, cus, &g->plan, &g->plan2, &g->use2);
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(std::make_tuple(v.n0, v.n1, v.n2));
         if (it != g_tuned.end()) {
             const Tuned& c = it->second;
             g->plan = lbw::make_march_plan(v, c.tx, c.ty, c.lz, c.blocks);
             g->plan.nts = c.nts;
+            g->use2 = false;
             if (c.tx2 > 0 && lbw::march2_fits(v, c.tx2)) {
                 g->plan2 = lbw::make_march2_plan(v, c.tx2, c.ty2, c.lz2, c.blocks2);
                 g->use2 = true;
@@ -528,11 +530,14 @@ hipError_t launch_one(lbw_state* s, int from, hipStream_t st) {
 // The two-step pass applies: chosen for the geometry, no driven sources
 // (they are imposed between steps), and no tile of the pass holds more
 // probes than it records.
-bool two_step_ok(const lbw_state* s) {
+bool two_step_ok(lbw_state* s) {
     const lbw_geometry* g = s->g;
     if (!g->use2 || g->general || g->dev.dim != 3 || s->n_src > 0 || !lbw::march2_fits(g->dev, g->plan2.tx))
         return false;
-    if (s->n_probes == 0 || s->t >= s->t_max) return true;
+    if (s->n_probes <= lbw::march2_tile_probes() || s->t >= s->t_max) return true;
+    if (s->fit_version == g->plan_version) return s->probes_fit;
+    s->fit_version = g->plan_version;
+    s->probes_fit = false;
     std::map<int64_t, int> per_tile;
     const int64_t n0 = g->dev.n0, n1 = g->dev.n1;
     const lbw::MarchPlan& p = g->plan2;
@@ -555,6 +560,7 @@ bool two_step_ok(const lbw_state* s) {
         }
         if (++per_tile[tile] > lbw::march2_tile_probes()) return false;
     }
+    s->probes_fit = true;
     return true;
 }
 

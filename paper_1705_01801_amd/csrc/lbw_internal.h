@@ -110,7 +110,9 @@ struct MarchPlan {
 // the 256 MiB Infinity Cache.
 bool march_nts_default(const GeomDev& g);
 MarchPlan make_march_plan(const GeomDev& g, int tx, int ty, int lz, int blocks);
-int march_tx_for(int n0);
+// Launch shapes of a grid that has not been tuned: *one for single steps, and
+// *two where two steps per launch are expected to be faster (*use2).
+void choose_march_plans(const GeomDev& g, int cus, MarchPlan* one, MarchPlan* two, bool* use2);
 bool march_shape_ok(int tx, int ty);  // tx in {16, 32, 64}, tx * ty in {256, 512}
 int march_blocks_per_cu(int tx, int ty);
 hipError_t launch_step_march(const GeomDev& g, const ProbeArgs& pr, const MarchPlan& plan, const float* fin,

@@ -514,7 +514,6 @@ bool march_nts_default(const GeomDev& g) {
     return 2.0 * 4.0 * (2 * g.dim + 1) * (double)g.N > 256.0 * 1024.0 * 1024.0;
 }
 
-int march_tx_for(int n0) { return n0 <= 16 ? 16 : (n0 <= 32 ? 32 : 64); }
 
 bool march_shape_ok(int tx, int ty) {
     // 96- and 128-wide rows only with 4 or 8 of them (384 to 1024 threads):
@@ -656,6 +655,75 @@ hipError_t launch_step_batch(const BatchItem* items, const int32_t* tile_item, i
     else
         launch_batch_of<false, false>(items, tile_item, n_items, tiles_total, tx, section_nt, blocks, bp, fin, fout, st);
     return hipGetLastError();
+}
+
+// Launch shapes of a grid nobody has tuned, by the modelled time of a step in
+// microseconds.
+// One step per launch: a launch costs 3.5; a round of workgroups 1 + 0.85 lz
+// (a plane of the march is a round trip to the caches, so small grids want
+// short chunks on many workgroups); the traffic `node` per million nodes and
+// `lane` per million lanes, with 0.8 / lz more for the two boundary planes of
+// a chunk and up to a quarter more for the workgroups that the last round
+// leaves idle.  Grids in the Infinity Cache pay for lanes, those beyond it for
+// the rows: whole-row tiles store aligned, and rows of whole 128-byte lines
+// cost 3.5 less per million nodes.
+// Two steps per launch (balanced shares): 4, and per plane of the longest
+// share 0.4 + 0.010 n0 (tiles of 96) or 0.65 + 0.004 n0 (128).
+// The constants are fits to sweeps of every shape over 15 grids.  Measured
+// (32 or 64 wide tiles and chunks of 16, as before, in brackets): horn 24 x 48 x
+// 128 6.1 us (17.1), torus 37 x 61 x 113 8.2 (18.1), box 30 x 200 x 512 36.6
+// (38.5), cylinder 65 x 141 x 311 38.5 (43.5), box 200^3 151 (176), torus 60 x
+// 200 x 400 60.9 with two steps per launch (75.1), horn 91 x 220 x 390 89.8
+// (201), horn 120 x 250 x 400 120.8 (221).
+void choose_march_plans(const GeomDev& g, int cus, MarchPlan* one, MarchPlan* two, bool* use2) {
+    const double M = 1e-6, nodes = M * (double)g.N;
+    const bool hbm = march_nts_default(g), walled0 = g.bc_lo[0] != LBW_BC_PERIODIC;
+    double best = 1e30;
+    struct Shape {
+        int tx, ty;
+        double node, lane;  // in the Infinity Cache
+        double split, row;  // beyond it: per million nodes, rows split or whole
+    };
+    // (512 threads and more: slower in the cache, where there are not enough
+    // such tiles to go round)
+    static const Shape shapes[] = {{16, 16, 6.3, 5.3, 31.0, 12.0}, {32, 8, 6.3, 4.0, 23.0, 12.0},
+                                   {64, 4, 6.3, 4.0, 21.0, 11.0},  {64, 8, 0.0, 0.0, 20.0, 9.6},
+                                   {96, 8, 0.0, 0.0, 17.0, 10.0},  {128, 8, 0.0, 0.0, 17.0, 10.6}};
+    for (const Shape& s : shapes) {
+        if (!hbm && s.node == 0.0) continue;
+        const bool row = walled0 && g.n0 <= s.tx;
+        const int slots = cus * march_blocks_per_cu(s.tx, s.ty);
+        const double lanes = M * (double)((g.n0 + s.tx - 1) / s.tx * s.tx) * (double)((g.n1 + s.ty - 1) / s.ty * s.ty) *
+                             (double)g.n2;
+        const double work = hbm ? (row ? s.row + (g.n0 % 32 ? 3.5 : 0.0) : s.split) * nodes + lanes
+                                : s.node * nodes + s.lane * lanes;
+        for (int lz : {1, 2, 3, 4, 6, 8, 16, 32, 64}) {
+            if (lz > 1 && lz >= 2 * g.n2) continue;
+            const MarchPlan p = make_march_plan(g, s.tx, s.ty, lz, slots);
+            const double rounds = (double)((p.tiles + slots - 1) / slots);
+            const double idle = 1.0 - (double)p.tiles / (rounds * slots);
+            const double march = rounds * (1.0 + 0.85 * lz);
+            const double flow = work * (1.0 + 0.8 / lz) * (1.0 + 0.25 * idle / ((1.0 - idle) * rounds));
+            const double cost = 3.5 + (march > flow ? march : flow);
+            if (cost < best) {
+                best = cost;
+                *one = p;
+            }
+        }
+    }
+    *use2 = false;
+    for (const int tx : {96, 128}) {
+        const int ty = tx == 96 ? 6 : 4;
+        if (!march2_fits(g, tx)) continue;
+        const MarchPlan p = make_march2_plan(g, tx, ty, 0, cus * march2_blocks_per_cu(tx, ty));
+        const double share = (double)p.tiles / (double)p.blocks;
+        const double cost = 4.0 + (tx == 96 ? 0.4 + 0.010 * g.n0 : 0.65 + 0.004 * g.n0) * (share + 5.0);
+        if (cost < best) {
+            best = cost;
+            *two = p;
+            *use2 = true;
+        }
+    }
 }
 
 MarchPlan make_march_plan(const GeomDev& g, int tx, int ty, int lz, int blocks) {
