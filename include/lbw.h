@@ -460,8 +460,9 @@ int lbw_mlp_adam_step(lbw_mlp_t m, float lr, float beta1, float beta2, float eps
  * lr (1 + cos(pi s / steps)) / 2 + lr_floor at step s = 0 .. steps-1 of this
  * call, continuing the network's Adam state.  The rate and the bias
  * corrections are computed on the device from a step counter, in double as
- * a host would, and one step is captured once into a HIP graph and replayed
- * (no per-step host work).  loss (device, 1 float, may be NULL) receives the
+ * a host would; a step of a network of at most 8 layers, none wider than 256,
+ * is two launches, that of a larger one is captured once into a HIP graph
+ * and replayed.  loss (device, 1 float, may be NULL) receives the
  * loss of the last step's forward pass.  Synchronises.  Errors as
  * lbw_mlp_loss_grad and lbw_mlp_adam_step; steps < 1 is LBW_EINVAL. */
 int lbw_mlp_train(lbw_mlp_t m, const float* x, const float* t, const float* w, int B, float weight_sum, int steps,

@@ -9,11 +9,36 @@
 // are FP32; the output-layer gradient and the hidden-layer gradients are
 // rounded to BF16 before they enter a product.
 //
-// Every product is one kernel, gemm_kernel, with the elementwise work of the
-// layer fused into its epilogue: bias + tanh (hidden forward), bias (output
-// forward), bias + squared-error loss with the output gradient (training
-// forward), tanh backward (hidden gradient), and the bias gradient as the row
-// sums of the weight-gradient product.  A launch may carry two independent
+// Networks of up to 8 layers of at most 256 units (the surrogate's are 3-256-
+// 256-256-10) run in few launches, because at these sizes a launch costs more
+// than a layer:
+//  - rows_kernel takes 4 to 64 rows of the batch through all layers, the
+//    activations in LDS, and when training on through the loss and the
+//    gradients with respect to every layer's pre-activations, which are as
+//    local to a row as the forward pass is;
+//  - weights_kernel forms every layer's weight and bias gradient (sums over
+//    the batch) and applies Adam to them in its epilogue.
+// A forward pass is one launch, a training step two.  Both read every operand
+// with 16-byte loads: the weights are kept as two BF16 copies in the order in
+// which the forward and the backward products take them (frag_place),
+// and rows_kernel writes activations and gradients transposed, so that the
+// batch, over which weights_kernel sums, is contiguous.  The next layer's
+// weights are loaded while a layer's epilogue runs.  Both issue the products
+// of gemm_kernel below in its order, so the results are the same bits.
+// (The loss, a sum of FP32 shares, is added up in another order.)
+// Forward of 10,000 rows, 3-256-256-256-10: 74 us with a launch per layer, 14.5
+// so, of which the tanh of 7.7 million activations is about 12.  A training
+// step of 512 rows: 72 us in nine launches; 17 + 10 us in two.  rows_kernel is
+// bound by each CU reading every weight (0.85 us per 256 x 256 layer at 64
+// bytes a cycle) and by the chain of layers, weights_kernel by a trip to
+// memory for its operands.  Loading two layers ahead, and workgroups that only
+// warm the caches, made no difference.
+//
+// Larger networks: every product is one kernel, gemm_kernel, with the
+// elementwise work of the layer fused into its epilogue: bias + tanh (hidden
+// forward), bias (output forward), bias + squared-error loss with the output
+// gradient (training forward), tanh backward (hidden gradient), and the bias
+// gradient as the row sums of the weight-gradient product.  A launch may carry two independent
 // products (a layer's weight gradient and its input gradient), so a training
 // step is L forward launches, L backward launches and one Adam launch.
 //
@@ -29,6 +54,7 @@
 // their products, so a K of 128 costs one memory latency.
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "host_util.h"
@@ -218,6 +244,437 @@ __global__ __launch_bounds__(256) void gemm_kernel(Gemm g1, int n1, Gemm g2, Ext
     }
 }
 
+// ---- networks of few, small layers ----
+
+// Barrier that orders LDS accesses only: __syncthreads also waits for every
+// global load and store in flight, here the next layer's weights and the
+// transposed results.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+constexpr int kFewLayers = 8;
+constexpr int kFewWidth = 256;
+constexpr int kRowWaves = 16;              // waves of rows_kernel, one 16-column tile each
+constexpr int kLdw = kFewWidth + 8;        // LDS row of activations (padded: rows 4 banks apart)
+constexpr int kFragSteps = kFewWidth / 32;
+
+// Offsets of layer l: off parameters (W then b), fwd / bwd the two BF16
+// weight copies, xt its transposed input [w_l][Bp], dzt the transposed
+// gradient of its pre-activations [w_{l+1}][Bp] (Bp = B rounded up to 32).
+struct Net {
+    int L;
+    int w[kFewLayers + 1];
+    int64_t off[kFewLayers], fwd[kFewLayers], bwd[kFewLayers], xt[kFewLayers], dzt[kFewLayers];
+};
+
+// The kernel's first argument, a Net, copied to LDS by the workgroup (at
+// least 128 threads).
+__device__ __forceinline__ void net_to_lds(Net& out) {
+    constexpr int words = sizeof(Net) / 4;
+    static_assert(sizeof(Net) % 4 == 0 && words <= 128, "one word per thread");
+    const int* arg = (const int*)__builtin_amdgcn_kernarg_segment_ptr();
+    if (threadIdx.x < words) reinterpret_cast<int*>(&out)[threadIdx.x] = arg[threadIdx.x];
+}
+
+// Place of W[n][k] in the copies: 1 KB blocks of the 64 lanes' eight values of
+// one MFMA operand, (contraction step, output tile) in row-major order, so
+// that the steps beyond a layer's last lie beyond its copy.
+__host__ __device__ inline int64_t frag_place(int out, int con, int tiles) {
+    return (((int64_t)(con >> 5) * tiles + (out >> 4)) * 64 + ((con >> 3) & 3) * 16 + (out & 15)) * 8 + (con & 7);
+}
+__host__ __device__ inline int64_t frag_size(int out, int con) {
+    return (int64_t)((out + 15) / 16) * ((con + 31) / 32) * 512;
+}
+__device__ inline void put_weight(const Net& net, int l, int n, int k, float v, __bf16* __restrict__ wf) {
+    const int N = net.w[l + 1], K = net.w[l];
+    wf[net.fwd[l] + frag_place(n, k, (N + 15) / 16)] = (__bf16)v;
+    wf[net.bwd[l] + frag_place(k, n, (K + 15) / 16)] = (__bf16)v;
+}
+
+// Work of a training step that one thread does for all: the step counter,
+// and the learning rate and bias corrections of the step it now counts
+// (out[0..2]).  The rate follows the cosine schedule lr0 (1 + cos(pi s /
+// total)) / 2 + lr_floor with s = t - 1 - done0 the step within this run, and
+// the bias corrections are 1 - beta^t, in double.
+struct Schedule {
+    int64_t* counter;  // NULL: none
+    double lr0, lr_floor;
+    int64_t total, done0;
+    float b1, b2;
+    float* out;
+};
+__device__ inline void schedule_step(const Schedule& s) {
+    const int64_t t = *s.counter + 1;
+    *s.counter = t;
+    const double sfrac = (double)(t - 1 - s.done0) / (double)s.total;
+    s.out[0] = (float)(s.lr0 * 0.5 * (1.0 + cos(3.14159265358979323846 * sfrac)) + s.lr_floor);
+    s.out[1] = 1.0f - (float)pow((double)s.b1, (double)t);
+    s.out[2] = 1.0f - (float)pow((double)s.b2, (double)t);
+}
+
+// Rows [RV MT b, RV MT (b + 1)) of the batch, b = blockIdx.x, through all
+// layers.  An MFMA tile has 16 rows; with RV = 8 or 4 the rows repeat in it, and
+// the lanes that hold the same row divide the epilogue among them: it costs
+// more vector instructions (tanh) than the products do matrix ones, so a batch
+// that leaves CUs idle is better spread over them so.  TRAIN: t, w, inv as in Gemm; xt and dzt receive what
+// weights_kernel sums, partial[b] the block's share of the loss.  Else y
+// receives the outputs.
+template <bool TRAIN, int RV, int MT>
+__global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __bf16* __restrict__ wf,
+                                                              const float* __restrict__ par,
+                                                              const float* __restrict__ x, int B,
+                                                              float* __restrict__ y, const float* __restrict__ t,
+                                                              const float* __restrict__ w, float inv, int Bp,
+                                                              __bf16* __restrict__ tr, float* __restrict__ partial,
+                                                              Schedule sched) {
+    // activations and gradients of every layer when training, else the
+    // activations of two
+    constexpr int ROWS = RV * MT, J = RV / 4;  // J: values of a lane in a tile
+    static_assert(RV == 16 || MT == 1, "one tile of repeated rows");
+    __shared__ __align__(16) __bf16 act[TRAIN ? kFewLayers : 2][ROWS][kLdw];
+    __shared__ __align__(16) __bf16 grad[TRAIN ? kFewLayers : 1][TRAIN ? ROWS : 1][kLdw];
+    __shared__ float red[kRowWaves];
+    __shared__ Net nets;
+    __shared__ int4 desc[2 * kFewLayers + 1];
+    __shared__ float biases[kFewLayers][kFewWidth];
+    const int lane = threadIdx.x & 63, r = lane & 15, grp = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int b0 = blockIdx.x * ROWS;
+    // this lane's J rows of a tile are row0 .. row0 + J - 1, held in
+    // accumulator places j0 .. j0 + J - 1
+    const int j0 = RV == 16 ? 0 : RV == 8 ? 2 * (grp >> 1) : grp;
+    const int row0 = (4 * grp + j0) % RV;
+    const auto value = [&](const floatx4& a, int j) {
+        if constexpr (RV == 16) return a[j];
+        if constexpr (RV == 8) return grp < 2 ? a[j] : a[j + 2];
+        const float lo = grp & 1 ? a[1] : a[0], hi = grp & 1 ? a[3] : a[2];
+        return grp < 2 ? lo : hi;
+    };
+    if (TRAIN && b0 >= Bp) {
+        // one workgroup more than the batch takes: the schedule
+        if (threadIdx.x == 0) schedule_step(sched);
+        return;
+    }
+
+    // Phase p < L: layer p forward; phase L + i, when training: the gradient
+    // through layer L - 1 - i.  A phase's operand is this wave's column tile of
+    // a weight copy, loaded during the phase before: all eight steps, or two
+    // where those are enough (a CU takes 64 bytes a cycle from its cache, which
+    // is 0.85 us for a 256 x 256 layer whatever the number of rows; a load
+    // or a step behind a branch of its own is waited for at the join, 7.1 for
+    // 5.4 ms of 200 training steps, so the steps beyond a copy read as zero
+    // and are multiplied).
+    // The network's description, in LDS for indexing by phase:
+    net_to_lds(nets);
+    lds_barrier();
+    const int L = __builtin_amdgcn_readfirstlane(nets.L), phases = TRAIN ? 2 * L - 1 : L;
+    const int NO = __builtin_amdgcn_readfirstlane(nets.w[L]), rows = B - b0;
+    if (threadIdx.x < 2 * kFewLayers + 1) {
+        // phase -> bytes to its weight copy, bytes of it, columns, terms
+        const int p = threadIdx.x, q = p < phases ? p : phases - 1, l = q < L ? q : 2 * L - 1 - q;
+        const int N = nets.w[l + 1], K = nets.w[l], out = q < L ? N : K, con = q < L ? K : N;
+        desc[p] = make_int4(2 * (int)(q < L ? nets.fwd[l] : nets.bwd[l]), p < phases ? 2 * (int)frag_size(out, con) : 0,
+                            out, con);
+    }
+    // all biases
+    for (int i = threadIdx.x; i < L * kFewWidth; i += 64 * kRowWaves) {
+        const int l = i / kFewWidth, n = i % kFewWidth, N = nets.w[l + 1];
+        if (n < N) biases[l][n] = par[nets.off[l] + (int64_t)N * nets.w[l] + n];
+    }
+    lds_barrier();
+    struct Operand {
+        bf16x8 fr[kFragSteps];
+        int out, steps;
+    };
+    const auto load = [&](Operand& o, int p) {
+        const int4 d = desc[p];
+        const int out = __builtin_amdgcn_readfirstlane(d.z), tiles = (out + 15) / 16;
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(reinterpret_cast<const char*>(wf)) + __builtin_amdgcn_readfirstlane(d.x), (short)0,
+            __builtin_amdgcn_readfirstlane(d.y), 0x00020000);
+        o.out = out;
+        o.steps = wave < tiles ? (__builtin_amdgcn_readfirstlane(d.w) + 31) / 32 : 0;
+        const int at = wave * 1024 + lane * 16;
+        const auto block = [&](int s) {
+            o.fr[s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, at, s * tiles * 1024, 0));
+        };
+        if (o.steps > 2) {
+#pragma unroll
+            for (int s = 0; s < kFragSteps; ++s) block(s);
+        } else if (o.steps > 0) {
+            block(0);
+            block(1);
+        }
+    };
+    Operand o;
+    load(o, 0);
+    const int k0 = __builtin_amdgcn_readfirstlane(nets.w[0]);
+    for (int i = threadIdx.x; i < ROWS * kFewWidth; i += 64 * kRowWaves) {
+        const int m = i / kFewWidth, k = i % kFewWidth;
+        const bool ok = b0 + m < B && k < k0;
+        const float v = x[ok ? (int64_t)(b0 + m) * k0 + k : 0];
+        act[0][m][k] = ok ? (__bf16)v : (__bf16)0.0f;
+    }
+    // this lane's column, and the loss's targets and weights there
+    const int n = wave * 16 + r;
+    float tv[MT][J], wv[MT][J];
+    if constexpr (TRAIN)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int row = 16 * m + row0 + j;
+                const int64_t at = n < NO && row < rows ? (int64_t)(b0 + row) * NO + n : 0;
+                tv[m][j] = t[at];
+                wv[m][j] = 1.0f;
+                if (w) wv[m][j] = w[at];
+            }
+    lds_barrier();
+    float lsum = 0.f;
+    for (int p = 0; p < phases; ++p) {
+        const int l = p < L ? p : 2 * L - 1 - p;
+        const int out = o.out;
+        const __bf16(*in)[kLdw] = p < L ? act[TRAIN ? l : l & 1] : grad[TRAIN ? l : 0];
+        floatx4 acc[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        const auto step = [&](int s) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const bf16x8 a = *reinterpret_cast<const bf16x8*>(&in[16 * m + r % RV][32 * s + 8 * grp]);
+                acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, o.fr[s], acc[m], 0, 0, 0);
+            }
+        };
+        if (o.steps > 2) {
+#pragma unroll
+            for (int s = 0; s < kFragSteps; ++s) step(s);
+        } else if (o.steps > 0) {
+            step(0);
+            step(1);
+        }
+        load(o, p + 1);
+        // (every wave writes its columns, zeros beyond the layer's)
+        const bool nok = n < out;
+        if (p + 1 < L) {
+            const float bias = biases[l][n];
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    float z = 0.f;
+                    if (wave * 16 < out) z = tanhf(value(acc[m], j) + bias);
+                    act[TRAIN ? l + 1 : (l + 1) & 1][16 * m + row0 + j][n] =
+                        nok && 16 * m + row0 + j < rows ? (__bf16)z : (__bf16)0.0f;
+                }
+        } else if (p < L) {
+            const float bias = biases[l][n];
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const int row = 16 * m + row0 + j;
+                    const bool ok = nok && row < rows;
+                    const float yy = value(acc[m], j) + bias;
+                    if constexpr (TRAIN) {
+                        const float d = yy - tv[m][j];
+                        const float ww = wv[m][j];
+                        lsum += ok ? ww * d * d : 0.f;
+                        grad[l][row][n] = ok ? (__bf16)(2.0f * ww * d * inv) : (__bf16)0.0f;
+                    } else if (ok) {
+                        y[(int64_t)(b0 + row) * NO + n] = yy;
+                    }
+                }
+        } else if constexpr (TRAIN) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const int row = 16 * m + row0 + j;
+                    const float yy = (float)act[l][row][n];
+                    const float v = value(acc[m], j);
+                    grad[l - 1][row][n] = nok && row < rows ? (__bf16)(v * (1.0f - yy * yy)) : (__bf16)0.0f;
+                }
+        }
+        lds_barrier();
+    }
+    if constexpr (TRAIN) {
+        // everything transposed: ROWS batch values of a column at a time
+        typedef __bf16 bf16xr __attribute__((ext_vector_type(ROWS)));
+        for (int l = 0; l < L; ++l)
+            for (int i = threadIdx.x; i < nets.w[l] + nets.w[l + 1]; i += 64 * kRowWaves) {
+                const bool x_part = i < nets.w[l];
+                const int c = x_part ? i : i - nets.w[l];
+                bf16xr q;
+#pragma unroll
+                for (int row = 0; row < ROWS; ++row) q[row] = x_part ? act[l][row][c] : grad[l][row][c];
+                *reinterpret_cast<bf16xr*>(tr + (x_part ? nets.xt[l] : nets.dzt[l]) + (int64_t)c * Bp + b0) = q;
+            }
+        lsum = wave_sum(lsum);
+        if (lane == 0) red[wave] = lsum;
+        lds_barrier();
+        if (threadIdx.x == 0) {
+            float s = 0.f;
+            for (int i = 0; i < kRowWaves; ++i) s += red[i];
+            partial[blockIdx.x] = s;
+        }
+    }
+}
+
+// One Adam update (FP32): parameter p, moments m and v (updated), gradient gi;
+// returns the new parameter.
+__device__ __forceinline__ float adam_value(float p, float& m, float& v, float gi, float lr, float b1, float b2,
+                                            float eps, float c1, float c2) {
+    const float mi = b1 * m + (1.0f - b1) * gi;
+    const float vi = b2 * v + (1.0f - b2) * gi * gi;
+    m = mi;
+    v = vi;
+    return p - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+}
+
+// The update of parameter i in memory.
+__device__ __forceinline__ float adam_update(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
+                                             int64_t i, float gi, float lr, float b1, float b2, float eps, float c1,
+                                             float c2) {
+    float mi = m[i], vi = v[i];
+    const float pi = adam_value(p[i], mi, vi, gi, lr, b1, b2, eps, c1, c2);
+    m[i] = mi;
+    v[i] = vi;
+    p[i] = pi;
+    return pi;
+}
+
+// Weight and bias gradients of every layer, dW = dz^T X and db = row sums of
+// dz^T over the batch (B rounded up to 32), one 32 x 32 tile per workgroup;
+// with `rate` (learning rate and bias corrections of this step) Adam follows
+// at once.  Workgroup 0 also adds up the loss.
+__global__ __launch_bounds__(256) void weights_kernel(Net net, const __bf16* __restrict__ tr, int Bp,
+                                                      float* __restrict__ g, float* __restrict__ p,
+                                                      float* __restrict__ m1, float* __restrict__ v1,
+                                                      __bf16* __restrict__ wf, const float* __restrict__ rate,
+                                                      float b1, float b2, float eps, Extra x) {
+    constexpr int kSteps = 16;
+    __shared__ Net nets;
+    net_to_lds(nets);
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int r = lane & 15, grp = lane >> 4;
+    int l = 0, id = blockIdx.x, tm = (nets.w[1] + 31) / 32;
+    for (; l + 1 < nets.L; ++l, tm = (nets.w[l + 1] + 31) / 32) {
+        const int n = tm * ((nets.w[l] + 31) / 32);
+        if (id < n) break;
+        id -= n;
+    }
+    l = __builtin_amdgcn_readfirstlane(l);
+    id = __builtin_amdgcn_readfirstlane(id);
+    tm = __builtin_amdgcn_readfirstlane(tm);
+    const int M = __builtin_amdgcn_readfirstlane(nets.w[l + 1]), N = __builtin_amdgcn_readfirstlane(nets.w[l]);
+    const int64_t off = nets.off[l];
+    const int m0 = (id % tm) * 32 + (wave & 1) * 16, n0 = (id / tm) * 32 + (wave >> 1) * 16;
+    // rows m0 + r of dz^T and n0 + r of X^T, eight batch values of group grp
+    const bool aok = m0 + r < M, bok = n0 + r < N;
+    const __bf16* __restrict__ A = tr + nets.dzt[l] + (int64_t)(aok ? m0 + r : 0) * Bp + 8 * grp;
+    const __bf16* __restrict__ X = tr + nets.xt[l] + (int64_t)(bok ? n0 + r : 0) * Bp + 8 * grp;
+    const bool sums = n0 == 0;
+    bf16x8 ones;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.0f;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f}, accs = {0.f, 0.f, 0.f, 0.f};
+    const auto masked = [](uint4 v, bool ok) {
+        v.x = ok ? v.x : 0u;
+        v.y = ok ? v.y : 0u;
+        v.z = ok ? v.z : 0u;
+        v.w = ok ? v.w : 0u;
+        return __builtin_bit_cast(bf16x8, v);
+    };
+    const int steps = Bp / 32;
+    uint4 ra[kSteps], rb[kSteps];
+    const auto load = [&](int s0) {
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            const int s = s0 + u < steps ? s0 + u : steps - 1;  // (past the end: loaded, not used)
+            ra[u] = *reinterpret_cast<const uint4*>(A + 32 * s);
+            rb[u] = *reinterpret_cast<const uint4*>(X + 32 * s);
+        }
+    };
+    load(0);
+    // Adam's operands, on their way during the products
+    const int n = n0 + r;
+    float pv[4], mv[4], vv[4], lr = 0.f, c1 = 1.f, c2 = 1.f;
+    if (rate) {
+        lr = rate[0];
+        c1 = rate[1];
+        c2 = rate[2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int m = m0 + 4 * grp + j;
+            const int64_t i = m < M && n < N ? off + (int64_t)m * N + n : 0;
+            pv[j] = p[i];
+            mv[j] = m1[i];
+            vv[j] = v1[i];
+        }
+    }
+    for (int s0 = 0; s0 < steps; s0 += kSteps) {
+        bf16x8 a[kSteps], b[kSteps];
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            a[u] = masked(ra[u], aok);
+            b[u] = masked(rb[u], bok);
+        }
+        if (s0 + kSteps < steps) load(s0 + kSteps);
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+            if (s0 + u < steps) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], b[u], acc, 0, 0, 0);
+                if (sums) accs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], ones, accs, 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int m = m0 + 4 * grp + j;
+        if (m < M && n < N) {
+            const int64_t i = off + (int64_t)m * N + n;
+            g[i] = acc[j];
+            if (rate) {
+                const float pi = adam_value(pv[j], mv[j], vv[j], acc[j], lr, b1, b2, eps, c1, c2);
+                p[i] = pi;
+                m1[i] = mv[j];
+                v1[i] = vv[j];
+                put_weight(nets, l, m, n, pi, wf);
+            }
+        }
+        if (m < M && sums && r == 0) {
+            const int64_t i = off + (int64_t)M * N + m;
+            g[i] = accs[j];
+            if (rate) adam_update(p, m1, v1, i, accs[j], lr, b1, b2, eps, c1, c2);
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 64 && x.fin_partial) {
+        float s = 0.f;
+        for (int i = threadIdx.x; i < x.fin_n; i += 64) s += x.fin_partial[i];
+        s = wave_sum(s);
+        if (threadIdx.x == 0) x.fin_loss[0] = s * x.fin_inv;
+    }
+}
+
+// The weight copies from the FP32 parameters (n of them); with grad, after an
+// Adam update of each.
+__global__ void copies_kernel(Net net, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
+                              float* __restrict__ v, __bf16* __restrict__ wf, int64_t n, float lr, float b1, float b2,
+                              float eps, float c1, float c2) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const float pi = g ? adam_update(p, m, v, i, g[i], lr, b1, b2, eps, c1, c2) : p[i];
+    int l = 0;
+    while (l + 1 < net.L && i >= net.off[l + 1]) ++l;
+    const int64_t q = i - net.off[l];
+    const int K = net.w[l];
+    if (q < (int64_t)net.w[l + 1] * K) put_weight(net, l, (int)(q / K), (int)(q % K), pi, wf);
+}
+
 __global__ void to_bf16_kernel(const float* __restrict__ in, __bf16* __restrict__ out, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) out[i] = (__bf16)in[i];
@@ -230,14 +687,7 @@ __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, 
                             float eps, float c1, float c2) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    p[i] = pi;
-    pb[i] = (__bf16)pi;
+    pb[i] = (__bf16)adam_update(p, m, v, i, g[i], lr, b1, b2, eps, c1, c2);
 }
 
 // The same update inside a replayed training step: the step index t (from 1)
@@ -255,14 +705,7 @@ __global__ void adam_sched_kernel(float* __restrict__ p, const float* __restrict
     const float lr = (float)(lr0 * 0.5 * (1.0 + cos(3.14159265358979323846 * sfrac)) + lr_floor);
     const float c1 = 1.0f - (float)pow((double)b1, (double)t);
     const float c2 = 1.0f - (float)pow((double)b2, (double)t);
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    p[i] = pi;
-    pb[i] = (__bf16)pi;
+    pb[i] = (__bf16)adam_update(p, m, v, i, g[i], lr, b1, b2, eps, c1, c2);
 }
 
 __global__ void count_set_kernel(int64_t* c, int64_t value) {
@@ -334,6 +777,16 @@ struct lbw_mlp {
     int n_partial = 0;
     float* loss_dev = nullptr;
     int64_t* d_steps = nullptr;  // Adam steps taken, on the device (scheduled training)
+    // networks of few, small layers: the weight copies, the transposed
+    // activations and gradients of a training step (offsets for batch Bp),
+    // and the rate and bias corrections of the step
+    bool few = false;
+    int cus = 256;
+    Net net{};
+    __bf16* wf = nullptr;
+    int64_t wf_size = 0;
+    __bf16* tr = nullptr;
+    float* rate = nullptr;
     int64_t steps = 0;
     bool have_grad = false;
 };
@@ -341,6 +794,11 @@ struct lbw_mlp {
 namespace {
 
 hipError_t refresh_bf16(lbw_mlp* M) {
+    if (M->few) {
+        hipLaunchKernelGGL(copies_kernel, dim3(nblk(M->P)), dim3(256), 0, M->stream, M->net, M->p, nullptr, nullptr,
+                           nullptr, M->wf, M->P, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(to_bf16_kernel, dim3(nblk(M->P)), dim3(256), 0, M->stream, M->p, M->wb, M->P);
     return hipGetLastError();
 }
@@ -418,6 +876,68 @@ hipError_t backward(lbw_mlp* M, int B, float inv, hipStream_t st) {
     return e;
 }
 
+int rows32(int B) { return (B + 31) / 32 * 32; }
+
+// Offsets of the transposed arrays for a batch of B rows.
+Net net_for(const lbw_mlp* M, int B) {
+    Net net = M->net;
+    const int64_t Bp = rows32(B);
+    int64_t at = 0;
+    for (int l = 0; l < net.L; ++l) {
+        net.xt[l] = at;
+        at += net.w[l] * Bp;
+        net.dzt[l] = at;
+        at += net.w[l + 1] * Bp;
+    }
+    return net;
+}
+
+// Outputs y of B rows of x, one launch: as many rows per workgroup, 4 to 64,
+// as give each CU one workgroup (each reads all the weights, and a second
+// round of workgroups costs as much as the first).
+template <int RV, int MT>
+void launch_rows(lbw_mlp* M, const float* x, int B, float* y) {
+    hipLaunchKernelGGL((rows_kernel<false, RV, MT>), dim3((B + RV * MT - 1) / (RV * MT)), dim3(64 * kRowWaves), 0,
+                       M->stream, M->net, M->wf, M->p, x, B, y, nullptr, nullptr, 0.f, 0, nullptr, nullptr,
+                       Schedule{});
+}
+hipError_t few_forward(lbw_mlp* M, const float* x, int B, float* y) {
+    const int cus = M->cus;
+    if (B <= 4 * cus) launch_rows<4, 1>(M, x, B, y);
+    else if (B <= 8 * cus) launch_rows<8, 1>(M, x, B, y);
+    else if (B <= 16 * cus) launch_rows<16, 1>(M, x, B, y);
+    else if (B <= 32 * cus) launch_rows<16, 2>(M, x, B, y);
+    else if (B <= 48 * cus) launch_rows<16, 3>(M, x, B, y);
+    else launch_rows<16, 4>(M, x, B, y);
+    return hipGetLastError();
+}
+
+// Loss and gradients, and with a schedule the Adam step: two launches.
+hipError_t few_train(lbw_mlp* M, const Net& net, const float* x, const float* t, const float* w, int B, float inv,
+                     const Schedule& sched, float eps) {
+    const int Bp = rows32(B);
+    int rows = 16;  // per workgroup, as few_forward
+    const auto launch = [&](auto rv) {
+        constexpr int RV = decltype(rv)::value;
+        rows = RV;
+        hipLaunchKernelGGL((rows_kernel<true, RV, 1>), dim3(Bp / RV + (sched.counter ? 1 : 0)), dim3(64 * kRowWaves),
+                           0, M->stream, net, M->wf, M->p, x, B, nullptr, t, w, inv, Bp, M->tr, M->partial, sched);
+    };
+    if (Bp <= 4 * M->cus) launch(std::integral_constant<int, 4>{});
+    else if (Bp <= 8 * M->cus) launch(std::integral_constant<int, 8>{});
+    else launch(std::integral_constant<int, 16>{});
+    int tiles = 0;
+    for (int l = 0; l < net.L; ++l) tiles += ((net.w[l + 1] + 31) / 32) * ((net.w[l] + 31) / 32);
+    Extra fin{};
+    fin.fin_partial = M->partial;
+    fin.fin_n = Bp / rows;
+    fin.fin_inv = inv;
+    fin.fin_loss = M->loss_dev;
+    hipLaunchKernelGGL(weights_kernel, dim3(tiles), dim3(256), 0, M->stream, net, M->tr, Bp, M->g, M->p, M->m, M->v,
+                       M->wf, sched.counter ? M->rate : nullptr, sched.b1, sched.b2, eps, fin);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 extern "C" {
@@ -445,18 +965,44 @@ int lbw_mlp_create(const int32_t* widths, int n_layers, int max_batch, void* str
     }
     M->P = P;
     const int64_t bw = (int64_t)max_batch * maxw;
+    // (the last bound: offsets of rows x width elements stay within 32 bits)
+    M->few = n_layers <= kFewLayers && maxw <= kFewWidth && max_batch <= (1 << 22);
+    int64_t T = 0;
+    if (M->few) {
+        if (lbw::device_cus(&M->cus) != LBW_OK) M->cus = 256;
+        M->net.L = n_layers;
+        for (int l = 0; l <= n_layers; ++l) M->net.w[l] = M->w[l];
+        for (int l = 0; l < n_layers; ++l) {
+            M->net.off[l] = M->off[l];
+            M->net.fwd[l] = M->wf_size;
+            M->wf_size += frag_size(M->w[l + 1], M->w[l]);
+            M->net.bwd[l] = M->wf_size;
+            M->wf_size += frag_size(M->w[l], M->w[l + 1]);
+            T += (int64_t)(M->w[l] + M->w[l + 1]) * rows32(max_batch);
+        }
+    }
     hipError_t e = hipMalloc(&M->p, sizeof(float) * P);
     if (e == hipSuccess) e = hipMalloc(&M->g, sizeof(float) * P);
     if (e == hipSuccess) e = hipMalloc(&M->m, sizeof(float) * P);
     if (e == hipSuccess) e = hipMalloc(&M->v, sizeof(float) * P);
-    if (e == hipSuccess) e = hipMalloc(&M->wb, sizeof(__bf16) * P);
-    if (e == hipSuccess) e = hipMalloc(&M->act, sizeof(__bf16) * A);
-    if (e == hipSuccess) e = hipMalloc(&M->yout, sizeof(float) * (int64_t)max_batch * M->w[n_layers]);
-    if (e == hipSuccess) e = hipMalloc(&M->dz[0], sizeof(__bf16) * bw);
-    if (e == hipSuccess) e = hipMalloc(&M->dz[1], sizeof(__bf16) * bw);
-    // one loss sum per 32 x 32 output tile
-    if (e == hipSuccess)
-        e = hipMalloc(&M->partial, sizeof(float) * (((int64_t)max_batch + 31) / 32) * ((M->w[n_layers] + 31) / 32));
+    if (M->few) {
+        if (e == hipSuccess) e = hipMalloc(&M->wf, sizeof(__bf16) * M->wf_size);
+        if (e == hipSuccess) e = hipMemsetAsync(M->wf, 0, sizeof(__bf16) * M->wf_size, M->stream);
+        if (e == hipSuccess) e = hipMalloc(&M->tr, sizeof(__bf16) * T);
+        if (e == hipSuccess) e = hipMalloc(&M->rate, sizeof(float) * 3);
+        // one loss sum per 4 rows or more
+        if (e == hipSuccess) e = hipMalloc(&M->partial, sizeof(float) * (rows32(max_batch) / 4));
+    } else {
+        if (e == hipSuccess) e = hipMalloc(&M->wb, sizeof(__bf16) * P);
+        if (e == hipSuccess) e = hipMalloc(&M->act, sizeof(__bf16) * A);
+        if (e == hipSuccess) e = hipMalloc(&M->yout, sizeof(float) * (int64_t)max_batch * M->w[n_layers]);
+        if (e == hipSuccess) e = hipMalloc(&M->dz[0], sizeof(__bf16) * bw);
+        if (e == hipSuccess) e = hipMalloc(&M->dz[1], sizeof(__bf16) * bw);
+        // one loss sum per 32 x 32 output tile
+        if (e == hipSuccess)
+            e = hipMalloc(&M->partial,
+                          sizeof(float) * (((int64_t)max_batch + 31) / 32) * ((M->w[n_layers] + 31) / 32));
+    }
     if (e == hipSuccess) e = hipMalloc(&M->loss_dev, sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&M->d_steps, sizeof(int64_t));
     if (e == hipSuccess) e = hipMemsetAsync(M->p, 0, sizeof(float) * P, M->stream);
@@ -499,6 +1045,10 @@ int lbw_mlp_get_params(lbw_mlp_t M, float* host) {
 int lbw_mlp_forward(lbw_mlp_t M, const float* x, int B, float* y) {
     if (!M || !x || !y) return fail(LBW_EINVAL, "NULL argument");
     if (B < 1 || B > M->max_batch) return fail(LBW_EINVAL, "batch %d outside [1, %d]", B, M->max_batch);
+    if (M->few) {
+        HIP_TRY(few_forward(M, x, B, y), "lbw_mlp_forward");
+        return LBW_OK;
+    }
     HIP_TRY(cast_input(M, x, B, M->stream), "lbw_mlp_forward");
     HIP_TRY(forward_layers(M, B, y, nullptr, nullptr, 0.f, nullptr, M->stream), "lbw_mlp_forward");
     return LBW_OK;
@@ -510,9 +1060,13 @@ int lbw_mlp_loss_grad(lbw_mlp_t M, const float* x, const float* t, const float* 
     if (B < 1 || B > M->max_batch) return fail(LBW_EINVAL, "batch %d outside [1, %d]", B, M->max_batch);
     if (!(weight_sum > 0.0f)) return fail(LBW_EINVAL, "weight_sum must be > 0");
     const float inv = 1.0f / weight_sum;
-    HIP_TRY(cast_input(M, x, B, M->stream), "lbw_mlp_loss_grad");
-    HIP_TRY(forward_layers(M, B, nullptr, t, w, inv, nullptr, M->stream), "lbw_mlp_loss_grad");
-    HIP_TRY(backward(M, B, inv, M->stream), "lbw_mlp_loss_grad");
+    if (M->few) {
+        HIP_TRY(few_train(M, net_for(M, B), x, t, w, B, inv, Schedule{}, 0.f), "lbw_mlp_loss_grad");
+    } else {
+        HIP_TRY(cast_input(M, x, B, M->stream), "lbw_mlp_loss_grad");
+        HIP_TRY(forward_layers(M, B, nullptr, t, w, inv, nullptr, M->stream), "lbw_mlp_loss_grad");
+        HIP_TRY(backward(M, B, inv, M->stream), "lbw_mlp_loss_grad");
+    }
     if (loss) HIP_TRY(hipMemcpyAsync(loss, M->loss_dev, sizeof(float), hipMemcpyDeviceToDevice, M->stream), "loss");
     if (grad) HIP_TRY(hipMemcpyAsync(grad, M->g, sizeof(float) * M->P, hipMemcpyDeviceToDevice, M->stream), "grad");
     M->have_grad = true;
@@ -527,8 +1081,12 @@ int lbw_mlp_adam_step(lbw_mlp_t M, float lr, float beta1, float beta2, float eps
     M->steps += 1;
     const float c1 = 1.0f - (float)std::pow((double)beta1, (double)M->steps);
     const float c2 = 1.0f - (float)std::pow((double)beta2, (double)M->steps);
-    hipLaunchKernelGGL(adam_kernel, dim3(nblk(M->P)), dim3(256), 0, M->stream, M->p, M->g, M->m, M->v, M->wb, M->P,
-                       lr, beta1, beta2, eps, c1, c2);
+    if (M->few)
+        hipLaunchKernelGGL(copies_kernel, dim3(nblk(M->P)), dim3(256), 0, M->stream, M->net, M->p, M->g, M->m, M->v,
+                           M->wf, M->P, lr, beta1, beta2, eps, c1, c2);
+    else
+        hipLaunchKernelGGL(adam_kernel, dim3(nblk(M->P)), dim3(256), 0, M->stream, M->p, M->g, M->m, M->v, M->wb,
+                           M->P, lr, beta1, beta2, eps, c1, c2);
     HIP_TRY(hipGetLastError(), "lbw_mlp_adam_step");
     return LBW_OK;
 }
@@ -547,9 +1105,25 @@ int lbw_mlp_train(lbw_mlp_t M, const float* x, const float* t, const float* w, i
     // the loss, backward, Adam with the BF16 refresh) is captured on a
     // private stream and replayed on the network's stream
     const float inv = 1.0f / weight_sum;
-    HIP_TRY(cast_input(M, x, B, M->stream), "lbw_mlp_train");
+    if (!M->few) HIP_TRY(cast_input(M, x, B, M->stream), "lbw_mlp_train");
     hipLaunchKernelGGL(count_set_kernel, dim3(1), dim3(64), 0, M->stream, M->d_steps, M->steps);
     HIP_TRY(hipGetLastError(), "lbw_mlp_train");
+    if (M->few) {
+        // two launches per step, queued directly: they take longer to run
+        // than to queue
+        const Schedule sched{M->d_steps, lr, lr_floor, (int64_t)steps, M->steps, beta1, beta2, M->rate};
+        const Net net = net_for(M, B);
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < steps && e == hipSuccess; ++i) e = few_train(M, net, x, t, w, B, inv, sched, eps);
+        if (e == hipSuccess && loss)
+            e = hipMemcpyAsync(loss, M->loss_dev, sizeof(float), hipMemcpyDeviceToDevice, M->stream);
+        const hipError_t es = hipStreamSynchronize(M->stream);
+        if (e == hipSuccess) e = es;
+        if (e != hipSuccess) return hip_fail(e, "lbw_mlp_train");
+        M->steps += steps;
+        M->have_grad = true;
+        return LBW_OK;
+    }
     hipStream_t cap = nullptr;
     HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking), "lbw_mlp_train");
     hipGraph_t graph = nullptr;
@@ -585,7 +1159,7 @@ int lbw_mlp_free(lbw_mlp_t M) {
     (void)hipStreamSynchronize(M->stream);
     for (void* ptr : {(void*)M->p, (void*)M->g, (void*)M->m, (void*)M->v, (void*)M->wb, (void*)M->act,
                       (void*)M->yout, (void*)M->dz[0], (void*)M->dz[1], (void*)M->partial, (void*)M->loss_dev,
-                      (void*)M->d_steps})
+                      (void*)M->d_steps, (void*)M->wf, (void*)M->tr, (void*)M->rate})
         (void)hipFree(ptr);
     delete M;
     return LBW_OK;
