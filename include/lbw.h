@@ -379,13 +379,19 @@ int lbw_batch_get_step_config(lbw_batch_t b, int* tile_x, int* chunk_z, int* blo
  * with the other population store policy: non-temporal stores, the default
  * when the two population buffers exceed 256 MiB, or cached ones) with reps
  * steps each on scratch buffers, recording no probes and leaving
- * populations, step count and trace untouched, and keeps the fastest; best_us (may be NULL) receives its microseconds per step.
+ * populations, step count and trace untouched, and keeps the fastest; where
+ * every geometry fits a workgroup (see lbw_batch_step_n) many steps per launch
+ * are timed as well.  best_us (may be NULL) receives its microseconds per step.
  * Synchronises.  Errors: LBW_EINVAL (NULL batch, reps < 1), LBW_ENOMEM,
  * LBW_EDEVICE (the previous shape is kept). */
 int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us);
 int lbw_batch_set_graph_block(lbw_batch_t b, int steps);
 
-/* Queues n steps of every geometry (probes recorded) without waiting. */
+/* Queues n steps of every geometry (probes recorded) without waiting.  Where
+ * every geometry is small (at most 768 threads of 16 planes of one column
+ * each, 32 probes, 32 driven nodes), up to 32 steps are one launch, unless
+ * lbw_batch_set_step_config asked for a shape of single steps; the results,
+ * and the buffer that holds them, are the same. */
 int lbw_batch_step_n(lbw_batch_t b, int64_t n);
 
 /* Step count and the device buffer holding the current populations. */

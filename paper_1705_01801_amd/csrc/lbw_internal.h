@@ -203,6 +203,19 @@ hipError_t launch_step_batch(const BatchItem* items, const int32_t* tile_item, i
                              int tx, int section_nt, int blocks, bool nts, bool pery, const BatchProbeArgs& bp,
                              const float* fin, float* fout, hipStream_t st);
 
+// Up to kResidentSteps steps of every geometry of a batch in one launch, a
+// workgroup per geometry with its state on chip (step_resident.hip).  `run`
+// is the number of planes per thread (2 .. kResidentRun), `threads` the most
+// that resident_fits asks for over the geometries.  The result goes to fout,
+// which may be fin; the times are read from bank bp.parity and written to
+// that bank or, after an odd number of steps, the other.
+constexpr int kResidentSteps = 32, kResidentRun = 16;
+bool resident_fits(int n0, int n1, int n2, int n_probes, int run, int* threads);
+int resident_slot(int n0, int n1, int n2, int run, int64_t node);  // the thread that holds a node
+int resident_driven();  // driven nodes a geometry may have, at most one per thread
+hipError_t launch_step_resident(const BatchItem* items, int n_items, int run, int threads, bool pery,
+                                const BatchProbeArgs& bp, int steps, const float* fin, float* fout, hipStream_t st);
+
 // One driven node (Sec. IV.A/IV.C sources): its populations sit at
 // f[f_off + l N], l < q; the time is counters[counter].  kind 0 imposes a
 // pressure (a0 = amplitude w_0 sqrt(g), a1 = amplitude w sqrt(g)); kind

@@ -63,9 +63,8 @@ __device__ inline void bload7(__amdgpu_buffer_rsrc_t r, uint32_t N4, bool on, ui
 // Every kernel that imposes a source calls this, so a driven node gets the
 // same bits whichever kernel imposes it.
 template <int Q>
-__device__ inline void drive_node(int kind, double a0, double a1, double omega, int64_t t, float (&v)[Q]) {
+__device__ inline void drive_value(int kind, double a0, double a1, double s, float (&v)[Q]) {
 #pragma clang fp contract(off)
-    const double s = sin(omega * (double)t);
     if (kind == 0) {
         v[0] = (float)(a0 * s);
         const float u = (float)(a1 * s);
@@ -84,6 +83,10 @@ __device__ inline void drive_node(int kind, double a0, double a1, double omega, 
         if ((l - 1) / 2 == kind - 1) val += (l & 1) ? h : -h;
         v[l] = (float)val;
     }
+}
+template <int Q>
+__device__ inline void drive_node(int kind, double a0, double a1, double omega, int64_t t, float (&v)[Q]) {
+    drive_value<Q>(kind, a0, a1, sin(omega * (double)t), v);
 }
 
 // bload7 with the non-temporal hint when NTL
