@@ -85,6 +85,29 @@ constexpr int lds_s() {
     return RT ? 4 * NT + 8 : (NT / TX + 2) * (TX + 2) + 1;
 }
 
+// Coefficient rows of three planes in LDS, entries x0 - 1 .. x0 + TX and a
+// sink slot, one array per coefficient: c^2 Mhat00, 02, 22, 11,
+// c^2 Gamh0 / 2, c^2 Gamh2 / 2.  In tiles narrower than 64 columns a wave holds
+// several rows, whose lanes read the same entries, and the LDS serves equal
+// addresses in one pass only for reads of 4 bytes: a step of a 24 x 48 x 128
+// horn takes 6.2 us, with records of 32 bytes 6.5 (wider tiles: no difference).
+template <int TX>
+struct Rows {
+    float v[3][6][TX + 3];
+    __device__ void put(int slot, int i, const float4& lo, const float4& hi) {
+        v[slot][0][i] = lo.x;
+        v[slot][1][i] = lo.y;
+        v[slot][2][i] = lo.z;
+        v[slot][3][i] = lo.w;
+        v[slot][4][i] = hi.x;
+        v[slot][5][i] = hi.y;
+    }
+    __device__ float4 lo(int slot, int i) const {
+        return make_float4(v[slot][0][i], v[slot][1][i], v[slot][2][i], v[slot][3][i]);
+    }
+    __device__ float4 hi(int slot, int i) const { return make_float4(v[slot][4][i], v[slot][5][i], 0.f, 0.f); }
+};
+
 // One tile of one geometry: columns [x0, x0 + TX) x [y0, y0 + TY), planes
 // [z0, z0 + lz).  fin/fout point at the geometry's own population block.
 // RT: the tile is g.rtx x g.rty columns instead (at most NT of them, with
@@ -99,7 +122,7 @@ template <int TX, int NT, bool ROW, bool RT = false, bool NTS = false, bool SRC 
           bool PERY = false>
 __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const float* __restrict__ fin,
                                            float* __restrict__ fout, float (&sS)[2][lds_s<TX, NT, RT>()],
-                                           float4 (&sElo)[3][TX + 3], float4 (&sEhi)[3][TX + 3]) {
+                                           Rows<TX>& sE) {
     const int TXr = RT ? g.rtx : TX;
     const int TY = RT ? g.rty : NT / TX;
     const int W = TXr + 2;
@@ -219,12 +242,10 @@ __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const fl
             em = make_float2(e.y, e.z);
             Sc = sum7(fc);
             if (e0_on) {
-                sElo[0][threadIdx.x] = a0;
-                sEhi[0][threadIdx.x] = b0;
+                sE.put(0, threadIdx.x, a0, b0);
             }
             if (e1_on) {
-                sElo[1][threadIdx.x] = a1;
-                sEhi[1][threadIdx.x] = b1;
+                sE.put(1, threadIdx.x, a1, b1);
             }
             if (ring_on) sS[0][ring_lds] = sum7(rz);
             if (active) sS[0][my_lds] = Sc;
@@ -280,8 +301,8 @@ __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const fl
 
             const float* L = sS[sb];
             const float S = Sc;
-            const float4 e_lo = sElo[es][lx + 1];  // 00, 02, 22, 11
-            const float4 e_hi = sEhi[es][lx + 1];  // g0/2, g2/2, 0, 0
+            const float4 e_lo = sE.lo(es, lx + 1);  // 00, 02, 22, 11
+            const float4 e_hi = sE.hi(es, lx + 1);  // g0/2, g2/2, 0, 0
             // axis-0/1 neighbours: read unconditionally (every index is inside
             // the LDS arrays); collide() selects the wall rule
             Links k;
@@ -298,7 +319,7 @@ __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const fl
             k.wz_p = wz_p;
             k.wz_m = wz_m;
             float fs[7];
-            collide(fc, S, e_lo, e_hi, sElo[es][lx + 2], sElo[es][lx], sElo[es1][lx + 1], em, L[my_lds + 1],
+            collide(fc, S, e_lo, e_hi, sE.lo(es, lx + 2), sE.lo(es, lx), sE.lo(es1, lx + 1), em, L[my_lds + 1],
                     L[my_lds - 1], L[my_lds + W], L[my_lds - W], Sp, Sm, k, c2, two_w0, fs);
             const float cM02 = e_lo.y, cM22 = e_lo.z;
 
@@ -361,8 +382,7 @@ __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const fl
                 drive_loaded<SRC>(g, jz_p, ring_on, ring_col, r1);
                 // disabled lanes write the sink slot past the end (never read)
                 sS[sb ^ 1][ring_on ? ring_lds : kSinkS] = sum7(r1);
-                sElo[es2][e_on ? (int)threadIdx.x : TXr + 2] = e1[0];
-                sEhi[es2][e_on ? (int)threadIdx.x : TXr + 2] = e1[1];
+                sE.put(es2, e_on ? (int)threadIdx.x : TXr + 2, e1[0], e1[1]);
                 sS[sb ^ 1][active ? my_lds : kSinkS] = Sp;
                 Sm = Sc;
                 Sc = Sp;
@@ -387,8 +407,7 @@ __global__ __launch_bounds__(NT) void step_march_kernel(GeomDev g, ProbeArgs pr,
                                                               const float* __restrict__ fin,
                                                               float* __restrict__ fout) {
     __shared__ float sS[2][lds_s<TX, NT, false>()];
-    __shared__ float4 sElo[3][TX + 3];
-    __shared__ float4 sEhi[3][TX + 3];
+    __shared__ Rows<TX> sE;
     if (blockIdx.x == 0) record_probes<7>(g, pr, 1, fin);
     TileGeom tg;
     tg.n0 = g.n0;
@@ -415,7 +434,7 @@ __global__ __launch_bounds__(NT) void step_march_kernel(GeomDev g, ProbeArgs pr,
     const int t_begin = (int)(plan.tiles * xcd / kXcds);
     const int t_end = (int)(plan.tiles * (xcd + 1) / kXcds);
     for (int tile = t_begin + (int)blockIdx.x / kXcds; tile < t_end; tile += per_xcd_blocks)
-        march_tile<TX, NT, ROW, false, NTS, false, NTS, PERY>(tg, tile, fin, fout, sS, sElo, sEhi);
+        march_tile<TX, NT, ROW, false, NTS, false, NTS, PERY>(tg, tile, fin, fout, sS, sE);
 }
 
 // Batch of geometries advanced by one launch: tiles of all geometries form
@@ -432,8 +451,7 @@ __global__ __launch_bounds__(NT) void step_batch_kernel(const BatchItem* __restr
                                                          int64_t tiles_total, BatchProbeArgs bp,
                                                          const float* __restrict__ fin, float* __restrict__ fout) {
     __shared__ float sS[2][lds_s<TX, NT, SECTION>()];
-    __shared__ float4 sElo[3][TX + 3];
-    __shared__ float4 sEhi[3][TX + 3];
+    __shared__ Rows<TX> sE;
     // this launch's time per geometry: bank `parity`, which no block of it
     // writes (the probe blocks below write the other bank)
     const int64_t* __restrict__ t_now = bp.tcount + (size_t)bp.parity * n_items;
@@ -503,7 +521,7 @@ __global__ __launch_bounds__(NT) void step_batch_kernel(const BatchItem* __restr
         tg.src_zhi = it.src_zhi;
         tg.src_t = t_now[h];
         march_tile<TX, NT, true, SECTION, NTS, true, false, PERY>(tg, (int)(tile - it.tile_begin), fin + it.f_off,
-                                                     fout + it.f_off, sS, sElo, sEhi);
+                                                     fout + it.f_off, sS, sE);
     }
 }
 

@@ -55,8 +55,11 @@ struct M2Lds {
     float S[2][M2<TX, TY>::SROWS * M2<TX, TY>::W + 1];     // + a sink slot
     float X[4][M2<TX, TY>::XROWS * M2<TX, TY>::W + 1];
     float S1[2][M2<TX, TY>::S1ROWS * M2<TX, TY>::W + 1];
-    float4 Elo[6][M2<TX, TY>::W + 1];                      // coefficient rows, slot = (plane - za0) mod 6
-    float4 Ehi[6][M2<TX, TY>::W + 1];
+    // coefficient rows, slot = (plane - za0) mod 6: c^2 Mhat00, 02, 22, 11,
+    // c^2 Gamh0 / 2, c^2 Gamh2 / 2, an array each (96 x 256 x 512 torus: 104 us
+    // per step; with records of 16 bytes, whose ten reads per plane and wave
+    // were most of the LDS's time, 120)
+    float E[6][6][M2<TX, TY>::W + 1];
     float B[2][2][TY * TX + 1];                            // step B: +-e0 populations along the row (2 planes)
     int pnode[kTileProbes], px[kTileProbes], py[kTileProbes], pz[kTileProbes];
     int pcount;
@@ -178,9 +181,24 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     };
     auto stage_erow = [&](int slot, const float4& lo, const float4& hi) {
         if (erow_on) {
-            L.Elo[slot][threadIdx.x + 1] = lo;
-            L.Ehi[slot][threadIdx.x + 1] = hi;
+            float(&e)[6][W + 1] = L.E[slot];
+            const int i = (int)threadIdx.x + 1;
+            e[0][i] = lo.x;
+            e[1][i] = lo.y;
+            e[2][i] = lo.z;
+            e[3][i] = lo.w;
+            e[4][i] = hi.x;
+            e[5][i] = hi.y;
         }
+    };
+
+    auto elo = [&](int slot, int i) {
+        const float(&e)[6][W + 1] = L.E[slot];
+        return make_float4(e[0][i], e[1][i], e[2][i], e[3][i]);
+    };
+    auto ehi = [&](int slot, int i) {
+        const float(&e)[6][W + 1] = L.E[slot];
+        return make_float4(e[4][i], e[5][i], 0.f, 0.f);
     };
 
     // tile probes: those on the tile's own rows and planes record time t+1
@@ -324,10 +342,10 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
             zlinks(zr, k);
             if constexpr (PERZ) k.jz_p = k.jz_m = 0;  // (step A uses only their presence)
             const float* Ls = L.S[sb];
-            const float4 e_lo = L.Elo[K % 6][lx + 1], e_hi = L.Ehi[K % 6][lx + 1];
-            const float4 enp = L.Elo[K % 6][lx + 2], enm = L.Elo[K % 6][lx];
-            const float4 ezp = L.Elo[(K + 1) % 6][lx + 1];
-            const float4 ezm = L.Elo[(K + 5) % 6][lx + 1];
+            const float4 e_lo = elo(K % 6, lx + 1), e_hi = ehi(K % 6, lx + 1);
+            const float4 enp = elo(K % 6, lx + 2), enm = elo(K % 6, lx);
+            const float4 ezp = elo((K + 1) % 6, lx + 1);
+            const float4 ezm = elo((K + 5) % 6, lx + 1);
             float fs[7];
             collide(fc, Sc, e_lo, e_hi, enp, enm, ezp, make_float2(ezm.y, ezm.z), Ls[my_s + 1], Ls[my_s - 1],
                     Ls[my_s + W], Ls[my_s - W], Sp, Sm, k, c2, two_w0, fs);
@@ -378,10 +396,10 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
             const float* L1 = L.S1[K & 1];  // plane z - 2
             // (threads off the tile's rows read row 1 instead: every index stays in the array)
             const int s1 = (actB ? ly : 1) * W + lx + 1;
-            const float4 e_lo = L.Elo[(K + 4) % 6][lx + 1], e_hi = L.Ehi[(K + 4) % 6][lx + 1];
-            const float4 enp = L.Elo[(K + 4) % 6][lx + 2], enm = L.Elo[(K + 4) % 6][lx];
-            const float4 ezp = L.Elo[(K + 5) % 6][lx + 1];
-            const float4 ezm = L.Elo[(K + 3) % 6][lx + 1];
+            const float4 e_lo = elo((K + 4) % 6, lx + 1), e_hi = ehi((K + 4) % 6, lx + 1);
+            const float4 enp = elo((K + 4) % 6, lx + 2), enm = elo((K + 4) % 6, lx);
+            const float4 ezp = elo((K + 5) % 6, lx + 1);
+            const float4 ezm = elo((K + 3) % 6, lx + 1);
             float fs[7];
             collide(f0, S1b, e_lo, e_hi, enp, enm, ezp, make_float2(ezm.y, ezm.z), L1[s1 + 1], L1[s1 - 1],
                     L1[s1 + W], L1[s1 - W], S1c, S1a, k, c2, two_w0, fs);
