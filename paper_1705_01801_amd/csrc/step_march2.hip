@@ -29,6 +29,12 @@
 //    steps, bit for bit;
 //  - probes: block 0 records time t from the input; the thread that owns a
 //    probe node records time t+1 from the state it assembled.
+// What bounds it: the latency of one plane (about 4900 cycles for 12 waves),
+// of which the vector unit is busy 28 %, the LDS 23 %; memory runs at 3.6 TB/s.
+// Offsets in memory are a lane constant plus a uniform part, and the walls of
+// axis 0 lane constants: 112 vector instructions per plane and wave instead of
+// 178, 100 us per step of a 96 x 256 x 512 torus instead of 104.  Loads two
+// planes ahead did not fit the registers (spills, 110 us).
 // Chunks along axis 2 are extended by two planes of step A either side (the
 // state at t+1 of planes z0-1 and z1 is needed), which is the price of the
 // chunking besides the two halo rows.
@@ -47,19 +53,19 @@ struct M2 {
     static constexpr int W = TX + 2;          // LDS row: one pad entry either side of the axis-0 row
     static constexpr int SROWS = TY + 6;      // S(t) of extended rows -2 .. TY+3
     static constexpr int XROWS = TY + 4;      // populations handed over by rows -1 .. TY+2
-    static constexpr int S1ROWS = TY + 2;     // S(t+1) of rows 0 .. TY+1
+    static constexpr int S1ROWS = TY + 4;     // S(t+1) of rows -1 .. TY+2 (the outer two unused)
 };
 
 template <int TX, int TY>
 struct M2Lds {
     float S[2][M2<TX, TY>::SROWS * M2<TX, TY>::W + 1];     // + a sink slot
-    float X[4][M2<TX, TY>::XROWS * M2<TX, TY>::W + 1];
-    float S1[2][M2<TX, TY>::S1ROWS * M2<TX, TY>::W + 1];
+    float X[4][M2<TX, TY>::XROWS * M2<TX, TY>::W + 1];     // (the last slot takes what nobody reads)
+    float S1[2][M2<TX, TY>::S1ROWS * M2<TX, TY>::W];
     // coefficient rows, slot = (plane - za0) mod 6: c^2 Mhat00, 02, 22, 11,
     // c^2 Gamh0 / 2, c^2 Gamh2 / 2, an array each (96 x 256 x 512 torus: 104 us
     // per step; with records of 16 bytes, whose ten reads per plane and wave
     // were most of the LDS's time, 120)
-    float E[6][6][M2<TX, TY>::W + 1];
+    float E[6][6 * M2<TX, TY>::W + 1];                     // + a sink slot
     float B[2][2][TY * TX + 1];                            // step B: +-e0 populations along the row (2 planes)
     int pnode[kTileProbes], px[kTileProbes], py[kTileProbes], pz[kTileProbes];
     int pcount;
@@ -67,18 +73,27 @@ struct M2Lds {
 
 __device__ inline int wrap(int i, int n) { return ((i % n) + n) % n; }
 
-// The lane's link indices (axis 0, axis 1) and activity flags passed
-// through an empty asm statement once per plane: the compiler then derives
-// the lane masks it selects with where they are used, instead of keeping
-// them all in scalar registers for the whole march (more than the scalar
-// file holds: the rest would be spilled to vector lanes and read back twice
-// per use).
-__device__ __forceinline__ void opaque_jx(Links& k) { asm volatile("" : "+v"(k.jx_p), "+v"(k.jx_m)); }
+// The lane's link indices along axis 1 passed through an empty asm statement
+// once per plane: the compiler then derives the lane masks it selects with
+// where they are used, instead of keeping them all in scalar registers for the
+// whole march (more than the scalar file holds: the rest would be spilled to
+// vector lanes and read back twice per use).
 __device__ __forceinline__ void opaque_jy(Links& k) { asm volatile("" : "+v"(k.jy_p), "+v"(k.jy_m)); }
-__device__ __forceinline__ bool opaque_bool(bool b) {
-    int v = b;
-    asm volatile("" : "+v"(v));
-    return v != 0;
+
+// Loads and stores with a lane part (kOff in disabled lanes) and a uniform
+// part of the offset: a plane's address costs the vector unit nothing.  The
+// uniform part is below 7 N4 < 2^31, so a disabled lane's sum stays out of
+// range and does not wrap.
+__device__ __forceinline__ float bldu(__amdgpu_buffer_rsrc_t r, uint32_t lane, uint32_t uni) {
+    return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)lane, (int)uni, 0));
+}
+__device__ __forceinline__ void bstu(__amdgpu_buffer_rsrc_t r, uint32_t lane, uint32_t uni, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), r, (int)lane, (int)uni, 0);
+}
+__device__ __forceinline__ void bload7u(__amdgpu_buffer_rsrc_t r, uint32_t N4, uint32_t lane, uint32_t uni,
+                                        float v[7]) {
+#pragma unroll
+    for (int l = 0; l < 7; ++l) v[l] = bldu(r, lane, uni + (uint32_t)l * N4);
 }
 
 // PERY, PERZ: axis 1, axis 2 is periodic (every link along it present;
@@ -118,7 +133,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     kl.jy_p = ypres ? link_coord(ya, +1, n1, g.bc_lo[1], g.bc_hi[1], &kl.wy_p) : -1;
     kl.jy_m = ypres ? link_coord(ya, -1, n1, g.bc_lo[1], g.bc_hi[1], &kl.wy_m) : -1;
     const uint32_t col4 = actA ? ((uint32_t)lx + (uint32_t)n0 * (uint32_t)ya) * 4u : 0u;
-    const int bcx_lo = g.bc_lo[0], bcx_hi = g.bc_hi[0], bcy_lo = g.bc_lo[1], bcy_hi = g.bc_hi[1];
+    const int bcy_lo = g.bc_lo[1], bcy_hi = g.bc_hi[1];
     // byte offsets to the axis-1 neighbours' columns (used where the link exists)
     const uint32_t dyp4 = (uint32_t)((kl.jy_p - ya) * n0) * 4u, dym4 = (uint32_t)((kl.jy_m - ya) * n0) * 4u;
 
@@ -132,22 +147,45 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     const bool ring_on = rpres && lx < n0;
     const bool ring_col = ring_on && rid < 2;  // collides its ring node
     Links kr{};
-    kr.jx_p = kl.jx_p;
-    kr.jx_m = kl.jx_m;
-    kr.wx_p = kl.wx_p;
-    kr.wx_m = kl.wx_m;
     kr.jy_p = rpres ? link_coord(rya, +1, n1, g.bc_lo[1], g.bc_hi[1], &kr.wy_p) : -1;
     kr.jy_m = rpres ? link_coord(rya, -1, n1, g.bc_lo[1], g.bc_hi[1], &kr.wy_m) : -1;
     const uint32_t ring4 = ring_on ? ((uint32_t)lx + (uint32_t)n0 * (uint32_t)rya) * 4u : 0u;
     const int my_s = (ly + 2) * W + lx + 1;                  // own S(t) slot
     const int ring_s = ring_on ? (re + 2) * W + lx + 1 : C::SROWS * W;
-    const int sinkS = C::SROWS * W;
+    const int xo = my_s - W;                                 // own slot of X and S1
 
-    // coefficient-row loader: thread t < n0 stages entry t (x = -1 and n0 are
-    // beyond the walls and never read)
-    const bool erow_on = (int)threadIdx.x < n0;
+    // The walls of axis 0 as lane constants instead of selections per plane:
+    // across a wall a lane reads its own S (negated for a fixed wall) and
+    // coefficients, and what the wall returns is a slot of its own in the
+    // hand-over times 1, damp or -1 (free walls: the population itself, else
+    // the opposite one)
+    const bool xp = kl.jx_p >= 0, xm = kl.jx_m >= 0;
+    const int sxp = my_s + (xp ? 1 : 0), sxm = my_s - (xm ? 1 : 0);
+    const int exo = lx + 1, exp = exo + (xp ? 1 : 0), exm = exo - (xm ? 1 : 0);
+    const bool free_p = g.bc_hi[0] == LBW_BC_FREE, free_m = g.bc_lo[0] == LBW_BC_FREE;
+    const float sg_p = !xp && g.bc_hi[0] == LBW_BC_FIXED ? -1.f : 1.f;
+    const float sg_m = !xm && g.bc_lo[0] == LBW_BC_FIXED ? -1.f : 1.f;
+    const float fac1 = xm || free_m ? 1.f : g.bc_lo[0] == LBW_BC_BOUNCEBACK ? damp : -1.f;
+    const float fac2 = xp || free_p ? 1.f : g.bc_hi[0] == LBW_BC_BOUNCEBACK ? damp : -1.f;
+    constexpr int XS = C::XROWS * W + 1, BS = TY * TX + 1;
+    const int ix1 = xm ? xo - 1 : free_m ? xo : XS + xo, ix2 = xp ? XS + xo + 1 : free_p ? XS + xo : xo;
+    const int bo = actB ? (ly - 1) * TX + lx : TY * TX;      // step B hand-over slot
+    const int ib1 = !actB ? TY * TX : xm ? bo - 1 : free_m ? bo : BS + bo;
+    const int ib2 = !actB ? TY * TX : xp ? BS + bo + 1 : free_p ? BS + bo : bo;
 
+    // lane parts of the offsets in memory
     const uint32_t N4 = N * 4u, plane4 = plane * 4u;
+    const uint32_t ownA = actA ? col4 : kOff, ownR = ring_on ? ring4 : kOff, ownB = actB ? col4 : kOff;
+    const uint32_t to3 = !actB ? kOff : kl.jy_p >= 0 ? 3u * N4 + col4 + dyp4 : 4u * N4 + col4;
+    const uint32_t to4 = !actB ? kOff : kl.jy_m >= 0 ? 4u * N4 + col4 + dym4 : 3u * N4 + col4;
+
+    // coefficient-row loader: a row is n0 records of 8 floats, 6 of them used;
+    // thread t loads and stages float t mod 6 of record t / 6
+    const int erec = (int)(threadIdx.x / 6u), ecoef = (int)(threadIdx.x % 6u);
+    const bool erow_on = erec < n0;
+    const uint32_t erow4 = erow_on ? (uint32_t)(erec * 32 + ecoef * 4) : kOff;
+    const int erow_s = erow_on ? ecoef * W + erec + 1 : 6 * W;
+
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(fin, 7u * N4);
     const __amdgpu_buffer_rsrc_t rout = make_rsrc(fout, 7u * N4);
     const __amdgpu_buffer_rsrc_t rtab = make_rsrc(g.tab, (uint32_t)n0 * (uint32_t)n2 * 32u);
@@ -173,32 +211,16 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
         k.jz_m = dn ? r - 1 : jzm_end;
         k.wz_m = dn ? 0 : wzm_end;
     };
-    auto erow_r = [&](int zr, float4& lo, float4& hi) {
-        const bool on = erow_on && zr >= 0;
-        const uint32_t off = on ? (uint32_t)(threadIdx.x + n0 * zr) * 32u : kOff;
-        lo = bld4(rtab, off);
-        hi = bld4(rtab, on ? off + 16u : kOff);
-    };
-    auto stage_erow = [&](int slot, const float4& lo, const float4& hi) {
-        if (erow_on) {
-            float(&e)[6][W + 1] = L.E[slot];
-            const int i = (int)threadIdx.x + 1;
-            e[0][i] = lo.x;
-            e[1][i] = lo.y;
-            e[2][i] = lo.z;
-            e[3][i] = lo.w;
-            e[4][i] = hi.x;
-            e[5][i] = hi.y;
-        }
-    };
-
+    // (a row beyond a wall is not read: any row does)
+    const uint32_t erow_bytes = (uint32_t)n0 * 32u;
+    auto erow_r = [&](int zr) { return bldu(rtab, erow4, (uint32_t)max(zr, 0) * erow_bytes); };
     auto elo = [&](int slot, int i) {
-        const float(&e)[6][W + 1] = L.E[slot];
-        return make_float4(e[0][i], e[1][i], e[2][i], e[3][i]);
+        const float* e = &L.E[slot][i];
+        return make_float4(e[0], e[W], e[2 * W], e[3 * W]);
     };
     auto ehi = [&](int slot, int i) {
-        const float(&e)[6][W + 1] = L.E[slot];
-        return make_float4(e[4][i], e[5][i], 0.f, 0.f);
+        const float* e = &L.E[slot][i];
+        return make_float4(e[4 * W], e[5 * W], 0.f, 0.f);
     };
 
     // tile probes: those on the tile's own rows and planes record time t+1
@@ -236,16 +258,13 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
         bload7(rin, N4, actA && zm >= 0, col4 + (uint32_t)zm * plane4, tmp);
         bload7(rin, N4, actA && zc >= 0, col4 + (uint32_t)zc * plane4, fA);
         bload7(rin, N4, ring_on && zc >= 0, ring4 + (uint32_t)zc * plane4, rA);
-        float4 a0, b0, a1, b1, a2, b2;
-        erow_r(rplane(za0 - 1), a0, b0);
-        erow_r(rplane(za0), a1, b1);
-        erow_r(rplane(za0 + 1), a2, b2);
+        const float e0 = erow_r(rplane(za0 - 1)), e1 = erow_r(rplane(za0)), e2 = erow_r(rplane(za0 + 1));
         Sm = sum7(tmp);
         Sc = sum7(fA);
-        stage_erow(5, a0, b0);  // plane za0 - 1
-        stage_erow(0, a1, b1);
-        stage_erow(1, a2, b2);
-        L.S[0][actA ? my_s : sinkS] = Sc;
+        L.E[5][erow_s] = e0;  // plane za0 - 1
+        L.E[0][erow_s] = e1;
+        L.E[1][erow_s] = e2;
+        L.S[0][my_s] = Sc;
         L.S[0][ring_s] = sum7(rA);
     }
     {
@@ -260,8 +279,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     // each plane stages the row loaded one plane earlier and loads the next
     // into the following slot (period three, by argument order, so no
     // register holding a load in flight is ever copied)
-    float4 eA[2], eB[2], eC[2];
-    erow_r(rplane(za0 + 2), eA[0], eA[1]);
+    float eA = erow_r(rplane(za0 + 2)), eB = 0.f, eC = 0.f;
     // real planes of march planes z, z + 2, z + 3 and z - 2 (carried along)
     int zrr = rplane(za0), zr2 = rplane(za0 + 2), zr3 = rplane(za0 + 3), zrb = rplane(za0 - 2);
 
@@ -275,19 +293,12 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     // step B's +-e0 stores of the previous plane, done after the next barrier
     // (the row hand-over through LDS then needs no barrier of its own)
     bool pend = false;
-    uint32_t pend_nb = 0;
-    float pend_v1w = 0.f, pend_v2w = 0.f;
-    int pend_slot = 0;
-    const int bo = (ly - 1) * TX + lx;  // step B hand-over slot
-    auto flush_pending = [&](const Links& k, bool onB) {
-        const float* B0 = L.B[pend_slot][0];
-        const float* B1 = L.B[pend_slot][1];
-        const float from_left = B0[lx > 0 && actB ? bo - 1 : TY * TX];
-        const float from_right = B1[lx < TX - 1 && actB ? bo + 1 : TY * TX];
-        const float in1 = k.jx_m >= 0 ? from_left : pend_v2w;
-        const float in2 = k.jx_p >= 0 ? from_right : pend_v1w;
-        bst(rout, pend && onB ? 1u * N4 + pend_nb : kOff, in1);
-        bst(rout, pend && onB ? 2u * N4 + pend_nb : kOff, in2);
+    uint32_t pend_z4 = 0;  // offset of that plane
+    int pend_slot = 0;     // (the loop passes it as a constant)
+    auto flush_pending = [&](int slot) {
+        const float* Bx = &L.B[slot][0][0];
+        bstu(rout, ownB, 1u * N4 + pend_z4, fac1 * Bx[ib1]);
+        bstu(rout, ownB, 2u * N4 + pend_z4, fac2 * Bx[ib2]);
     };
 
     const int zend = z1 + 2;
@@ -298,19 +309,18 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     // rc / rn / rnn the ring's; the caller rotates all of them by argument
     // order (period three), so no register is copied.
     auto march_plane = [&](float (&f0)[7], float (&f1)[7], float (&f2)[7], float (&fc)[7], float (&fnx)[7],
-                           float (&fnn)[7], float (&rc)[7], float (&rn)[7], float (&rnn)[7], float4 (&en)[2],
-                           float4 (&e3)[2], int z, auto kc) {
+                           float (&fnn)[7], float (&rc)[7], float (&rn)[7], float (&rnn)[7], float& en, float& e3,
+                           int z, auto kc) {
         constexpr int K = decltype(kc)::value;  // z - za0 modulo 6 (the loop runs six planes per turn)
         const int sb = K & 1;
         const bool doA = z < za1;
         const int zr = zrr;
         Links kp = kl, krp = kr;
-        // a wall code matters only where the link is missing, and there it
-        // is that end's code: every lane takes the end codes, uniform, so
-        // the wall rules are tested on the scalar unit
-        kp.wx_p = bcx_hi;
-        kp.wx_m = bcx_lo;
-        opaque_jx(kp);
+        // (the walls of axis 0 are in the slots: every link is there.)  A wall
+        // code matters only where the link is missing, and there it is that
+        // end's code: every lane takes the end codes, uniform, so the wall
+        // rules are tested on the scalar unit
+        kp.jx_p = kp.jx_m = kp.wx_p = kp.wx_m = 0;
         if constexpr (PERY) {
             kp.jy_p = kp.jy_m = kp.wy_p = kp.wy_m = 0;
             krp.jy_p = krp.jy_m = krp.wy_p = krp.wy_m = 0;
@@ -320,20 +330,19 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
             opaque_jy(kp);
             opaque_jy(krp);
         }
-        const bool pA = opaque_bool(actA), pB = opaque_bool(actB), pR = opaque_bool(ring_on);
         // loads consumed later: own column and ring of plane z+2 (S(t) of
-        // plane z+1 comes from fnx), coefficient row z+3
+        // plane z+1 comes from fnx), coefficient row z+3; beyond the last
+        // plane that is needed, plane z once more (not used)
         {
-            const int zq = zr2;
-            const bool on = z + 2 <= za1 && zq >= 0;
-            bload7(rin, N4, pA && on, col4 + (uint32_t)zq * plane4, fnn);
-            bload7(rin, N4, pR && on, ring4 + (uint32_t)zq * plane4, rnn);
+            const uint32_t zq4 = (uint32_t)(z + 2 <= za1 && zr2 >= 0 ? zr2 : max(zr, 0)) * plane4;
+            bload7u(rin, N4, ownA, zq4, fnn);
+            bload7u(rin, N4, ownR, zq4, rnn);
         }
-        erow_r(zr3, e3[0], e3[1]);
+        e3 = erow_r(zr3);
         Sp = sum7(fnx);
         const float Srp = sum7(rn);
         __syncthreads();  // S(t) of plane z, coefficient rows up to z+2, step B's hand-over visible
-        if (pend) flush_pending(kp, pB);  // uniform
+        if (pend) flush_pending((K + 1) & 1);  // uniform
         pend = false;
 
         if (doA) {
@@ -342,14 +351,13 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
             zlinks(zr, k);
             if constexpr (PERZ) k.jz_p = k.jz_m = 0;  // (step A uses only their presence)
             const float* Ls = L.S[sb];
-            const float4 e_lo = elo(K % 6, lx + 1), e_hi = ehi(K % 6, lx + 1);
-            const float4 enp = elo(K % 6, lx + 2), enm = elo(K % 6, lx);
-            const float4 ezp = elo((K + 1) % 6, lx + 1);
-            const float4 ezm = elo((K + 5) % 6, lx + 1);
+            const float4 e_lo = elo(K % 6, exo), e_hi = ehi(K % 6, exo);
+            const float4 enp = elo(K % 6, exp), enm = elo(K % 6, exm);
+            const float4 ezp = elo((K + 1) % 6, exo);
+            const float4 ezm = elo((K + 5) % 6, exo);
             float fs[7];
-            collide(fc, Sc, e_lo, e_hi, enp, enm, ezp, make_float2(ezm.y, ezm.z), Ls[my_s + 1], Ls[my_s - 1],
+            collide(fc, Sc, e_lo, e_hi, enp, enm, ezp, make_float2(ezm.y, ezm.z), sg_p * Ls[sxp], sg_m * Ls[sxm],
                     Ls[my_s + W], Ls[my_s - W], Sp, Sm, k, c2, two_w0, fs);
-            const int xo = (ly + 1) * W + lx + 1;  // hand-over slot of row ly
             L.X[0][xo] = fs[1];
             L.X[1][xo] = fs[2];
             L.X[2][xo] = fs[3];
@@ -365,13 +373,12 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
                 const int ro = (re + 1) * W + lx + 1;
                 // (row -1 sends f*_3 through X[2], row TY+2 f*_4 through X[3];
                 // one store by index, no branch)
-                constexpr int xs = C::XROWS * W + 1;
-                (&L.X[0][0])[(rid == 0 ? 2 * xs : 3 * xs) + (ring_col ? ro : C::XROWS * W)] = rid == 0 ? rs3 : rs4;
+                (&L.X[0][0])[(rid == 0 ? 2 * XS : 3 * XS) + (ring_col ? ro : C::XROWS * W)] = rid == 0 ? rs3 : rs4;
             }
             __syncthreads();  // handed-over populations visible
             f2[0] = fs[0];
-            f2[1] = k.jx_m >= 0 ? L.X[0][xo - 1] : bounce(k.wx_m, damp, fs[2], fs[1]);
-            f2[2] = k.jx_p >= 0 ? L.X[1][xo + 1] : bounce(k.wx_p, damp, fs[1], fs[2]);
+            f2[1] = fac1 * (&L.X[0][0])[ix1];
+            f2[2] = fac2 * (&L.X[0][0])[ix2];
             f2[3] = k.jy_m >= 0 ? L.X[2][xo - W] : bounce(k.wy_m, damp, fs[4], fs[3]);
             f2[4] = k.jy_p >= 0 ? L.X[3][xo + W] : bounce(k.wy_p, damp, fs[3], fs[4]);
             f2[5] = k.jz_m >= 0 ? carry5 : bounce(k.wz_m, damp, fs[6], fs[5]);
@@ -382,7 +389,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
         // plane z-1 is complete: its S(t+1) for step B's neighbours
         if (z - 1 >= za0 && z - 1 < za1) {
             S1c = sum7(f1);
-            L.S1[(K + 1) & 1][actA ? ly * W + lx + 1 : C::S1ROWS * W] = S1c;  // plane z - 1
+            L.S1[(K + 1) & 1][xo] = S1c;  // plane z - 1
         }
 
         // step B on plane zb = z - 2
@@ -394,15 +401,13 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
             const int jzp = k.jz_p, jzm = k.jz_m;  // the stores' planes
             if constexpr (PERZ) k.jz_p = k.jz_m = 0;
             const float* L1 = L.S1[K & 1];  // plane z - 2
-            // (threads off the tile's rows read row 1 instead: every index stays in the array)
-            const int s1 = (actB ? ly : 1) * W + lx + 1;
-            const float4 e_lo = elo((K + 4) % 6, lx + 1), e_hi = ehi((K + 4) % 6, lx + 1);
-            const float4 enp = elo((K + 4) % 6, lx + 2), enm = elo((K + 4) % 6, lx);
-            const float4 ezp = elo((K + 5) % 6, lx + 1);
-            const float4 ezm = elo((K + 3) % 6, lx + 1);
+            const float4 e_lo = elo((K + 4) % 6, exo), e_hi = ehi((K + 4) % 6, exo);
+            const float4 enp = elo((K + 4) % 6, exp), enm = elo((K + 4) % 6, exm);
+            const float4 ezp = elo((K + 5) % 6, exo);
+            const float4 ezm = elo((K + 3) % 6, exo);
             float fs[7];
-            collide(f0, S1b, e_lo, e_hi, enp, enm, ezp, make_float2(ezm.y, ezm.z), L1[s1 + 1], L1[s1 - 1],
-                    L1[s1 + W], L1[s1 - W], S1c, S1a, k, c2, two_w0, fs);
+            collide(f0, S1b, e_lo, e_hi, enp, enm, ezp, make_float2(ezm.y, ezm.z), sg_p * L1[sxp - W],
+                    sg_m * L1[sxm - W], L1[xo + W], L1[xo - W], S1c, S1a, k, c2, two_w0, fs);
             // probes at t+1 on this plane (the state f0 before step B)
             if (tile_probes > 0) {
                 for (int i = 0; i < tile_probes; ++i) {
@@ -417,26 +422,22 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
             // barrier (aligned stores); the rest to their destinations (or the
             // wall rules) now
             pend_slot = K & 1;
-            L.B[pend_slot][0][actB ? bo : TY * TX] = fs[1];
-            L.B[pend_slot][1][actB ? bo : TY * TX] = fs[2];
-            const uint32_t nb = col4 + (uint32_t)zbr * plane4;
+            L.B[K & 1][0][bo] = fs[1];
+            L.B[K & 1][1][bo] = fs[2];
+            const uint32_t z4 = (uint32_t)zbr * plane4;
             pend = true;
-            pend_nb = nb;
-            pend_v1w = bounce(k.wx_p, damp, fs[1], fs[2]);  // +e0 at the far wall, returned as -e0
-            pend_v2w = bounce(k.wx_m, damp, fs[2], fs[1]);  // -e0 at the near wall, returned as +e0
-            const uint32_t o3 = k.jy_p >= 0 ? 3u * N4 + nb + dyp4 : 4u * N4 + nb;
-            const uint32_t o4 = k.jy_m >= 0 ? 4u * N4 + nb + dym4 : 3u * N4 + nb;
-            const uint32_t o5 = k.jz_p >= 0 ? 5u * N4 + col4 + (uint32_t)jzp * plane4 : 6u * N4 + nb;
-            const uint32_t o6 = k.jz_m >= 0 ? 6u * N4 + col4 + (uint32_t)jzm * plane4 : 5u * N4 + nb;
+            pend_z4 = z4;
+            const uint32_t u5 = jzp >= 0 ? 5u * N4 + (uint32_t)jzp * plane4 : 6u * N4 + z4;
+            const uint32_t u6 = jzm >= 0 ? 6u * N4 + (uint32_t)jzm * plane4 : 5u * N4 + z4;
             const float v3 = k.jy_p >= 0 ? fs[3] : bounce(k.wy_p, damp, fs[3], fs[4]);
             const float v4 = k.jy_m >= 0 ? fs[4] : bounce(k.wy_m, damp, fs[4], fs[3]);
             const float v5 = k.jz_p >= 0 ? fs[5] : bounce(k.wz_p, damp, fs[5], fs[6]);
             const float v6 = k.jz_m >= 0 ? fs[6] : bounce(k.wz_m, damp, fs[6], fs[5]);
-            bst(rout, pB ? nb : kOff, fs[0]);
-            bst(rout, pB ? o3 : kOff, v3);
-            bst(rout, pB ? o4 : kOff, v4);
-            bst(rout, pB ? o5 : kOff, v5);
-            bst(rout, pB ? o6 : kOff, v6);
+            bstu(rout, ownB, z4, fs[0]);
+            bstu(rout, to3, z4, v3);
+            bstu(rout, to4, z4, v4);
+            bstu(rout, ownB, u5, v5);
+            bstu(rout, ownB, u6, v6);
         }
         S1a = S1b;
         S1b = S1c;
@@ -444,9 +445,9 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
         // stage S(t) of plane z+1 and the coefficient row z+2 for the next
         // march plane (their slots were last read two barriers ago)
         if (z + 1 < zend) {
-            L.S[sb ^ 1][actA ? my_s : sinkS] = Sp;
+            L.S[sb ^ 1][my_s] = Sp;
             L.S[sb ^ 1][ring_s] = Srp;
-            stage_erow((K + 2) % 6, en[0], en[1]);
+            L.E[(K + 2) % 6][erow_s] = en;
         }
         Sm = Sc;
         Sc = Sp;
@@ -471,7 +472,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
         ++z;
     }
     __syncthreads();  // the last plane's hand-over visible
-    if (pend) flush_pending(kl, actB);
+    if (pend) flush_pending(pend_slot);
     __syncthreads();  // LDS reuse by the next tile
 }
 
