@@ -294,6 +294,9 @@ int lbw_make_geometry_general(const lbw_geometry_desc* desc, const double* metri
         }
         t64[9 * N + n] = metric[n];
     }
+    int cus = 0;
+    rc = lbw::device_cus(&cus);
+    if (rc) return rc;
     lbw_geometry* g = new lbw_geometry();
     g->d = d;
     g->Q = 7;
@@ -316,11 +319,7 @@ int lbw_make_geometry_general(const lbw_geometry_desc* desc, const double* metri
     }
     g->dev = lbw::make_geomdev(d, g->tab32, g->tab64 + 9 * N);
     g->dev.sg_node = 1;
-    {
-        const int tx = g->dev.n0 > 32 ? 64 : 32;  // 64 x 8 or 32 x 8 tiles, 16 planes
-        g->plan = lbw::make_march_plan(g->dev, tx, 8, 16, 8);
-        g->plan.blocks = (int)g->plan.tiles;
-    }
+    lbw::choose_general_plan(g->dev, cus, &g->plan);
     *out = g;
     return LBW_OK;
 }

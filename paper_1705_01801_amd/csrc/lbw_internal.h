@@ -112,6 +112,7 @@ bool march_nts_default(const GeomDev& g);
 MarchPlan make_march_plan(const GeomDev& g, int tx, int ty, int lz, int blocks);
 // Launch shapes of a grid that has not been tuned: *one for single steps, and
 // *two where two steps per launch are expected to be faster (*use2).
+void choose_general_plan(const GeomDev& g, int cus, MarchPlan* plan);  // geometries given by their metric
 void choose_march_plans(const GeomDev& g, int cus, MarchPlan* one, MarchPlan* two, bool* use2);
 bool march_shape_ok(int tx, int ty);  // tx in {16, 32, 64}, tx * ty in {256, 512}
 int march_blocks_per_cu(int tx, int ty);

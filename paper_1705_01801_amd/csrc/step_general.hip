@@ -278,6 +278,27 @@ __global__ __launch_bounds__(NT) void general_march_kernel(GeomDev g, ProbeArgs 
 
 }  // namespace
 
+// 64 x 8 tiles of 16 planes where they give four fifths of the CUs a workgroup
+// (halo planes and rings then cost more than shorter chains save); else smaller
+// tiles of two planes, or of one where two leave CUs without a second workgroup,
+// for a chunk is a chain of 1.3 us a plane.  Per step, long chunks and short:
+// 20^3 nodes 21.9 and 4.6 us, 50^3 27.5 and 6.9, 40 x 80 x 100 25.2 and 9.6,
+// 128 x 64 x 128 28.9 and 19.9, 128 x 96 x 128 30.5 and 27.3; the long ones stay at
+// 128 x 104 x 128 (28.6 and 29.3) and above (128 x 120 x 128 31.5 and 33.0).
+void choose_general_plan(const GeomDev& g, int cus, MarchPlan* plan) {
+    const auto tiles = [&](int tx, int ty, int lz) {
+        return (int64_t)((g.n0 + tx - 1) / tx) * ((g.n1 + ty - 1) / ty) * ((g.n2 + lz - 1) / lz);
+    };
+    const int tx = g.n0 > 32 ? 64 : 32;
+    int ty = 8, lz = 16;
+    if (5 * tiles(tx, ty, lz) < 4 * (int64_t)cus) {
+        if (tx == 64) ty = 4;
+        lz = tiles(tx, ty, 2) >= 2 * (int64_t)cus ? 2 : 1;
+    }
+    *plan = make_march_plan(g, tx, ty, lz, 8);
+    plan->blocks = (int)plan->tiles;
+}
+
 hipError_t launch_step_general(const GeomDev& g, const ProbeArgs& pr, const MarchPlan& mp, const float* fin,
                                float* fout, hipStream_t st) {
     const int nt = mp.tx * mp.ty;
