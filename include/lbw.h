@@ -380,9 +380,9 @@ int lbw_batch_get_step_config(lbw_batch_t b, int* tile_x, int* chunk_z, int* blo
  * with the other population store policy: non-temporal stores, the default
  * when the two population buffers exceed 256 MiB, or cached ones) with reps
  * steps each on scratch buffers, recording no probes and leaving
- * populations, step count and trace untouched, and keeps the fastest; where
- * every geometry fits a workgroup (see lbw_batch_step_n) many steps per launch
- * are timed as well.  best_us (may be NULL) receives its microseconds per step.
+ * populations, step count and trace untouched, and keeps the fastest; timed as
+ * well are two steps per launch (walls on axis 0, 4 <= n0 <= 96, no driven nodes)
+ * and, where every geometry fits a workgroup (see lbw_batch_step_n), many.  best_us (may be NULL) receives its microseconds per step.
  * Synchronises.  Errors: LBW_EINVAL (NULL batch, reps < 1), LBW_ENOMEM,
  * LBW_EDEVICE (the previous shape is kept). */
 int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us);

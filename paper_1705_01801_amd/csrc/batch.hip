@@ -31,6 +31,12 @@ struct lbw_batch {
     // (0: some geometry does not fit) and threads; used where `resident` is set
     int run = 0, run_threads = 0;
     bool resident = false;
+    // two steps per launch: the segments that each workgroup marches (built
+    // and switched on by the tuner)
+    bool two = false;
+    lbw::BatchSegment* d_seg = nullptr;
+    int32_t* d_seg_begin = nullptr;  // first segment of each workgroup, blocks2 + 1 entries
+    int blocks2 = 0, threads2 = 0;
     float* f[2] = {nullptr, nullptr};
     int cur = 0;
     int64_t t = 0, t_max = 0;
@@ -74,6 +80,8 @@ void release(lbw_batch* b) {
     (void)hipFree(b->tab32);
     (void)hipFree(b->d_items);
     (void)hipFree(b->d_tile_item);
+    (void)hipFree(b->d_seg);
+    (void)hipFree(b->d_seg_begin);
     (void)hipFree(b->d_nodes);
     (void)hipFree(b->d_tcount);
     (void)hipFree(b->d_scratch_count);
@@ -111,6 +119,7 @@ hipError_t build_items(lbw_batch* b) {
         it.c2 = v.c2;
         it.two_w0 = v.two_w0;
         it.damp = v.damp;
+        it.rty2 = lbw::batch2_rows(v.n0, v.n1);
         it.rty = b->section_nt ? lbw::batch_row_tile(v.n0, v.n1, b->section_nt) : 0;
         it.ntx = b->section_nt ? 1 : (v.n0 + b->tx - 1) / b->tx;
         it.nty = b->section_nt ? (v.n1 + it.rty - 1) / it.rty : (v.n1 + ty - 1) / ty;
@@ -182,6 +191,102 @@ hipError_t launch_batch(lbw_batch* b, lbw::BatchProbeArgs bp, const float* fin, 
                                   b->pery, bp, fin, fout, st);
 }
 
+// Two steps, likewise.
+hipError_t launch_batch2(lbw_batch* b, lbw::BatchProbeArgs bp, const float* fin, float* fout, hipStream_t st) {
+    bp.parity = fin == b->f[1] ? 1 : 0;
+    return lbw::launch_step_batch2(b->d_items, b->d_seg, b->d_seg_begin, b->n, b->blocks2, b->threads2, b->pery, bp,
+                                   fin, fout, st);
+}
+
+bool two_steps(const lbw_batch* b) { return b->two && b->n_src == 0 && b->n_entries == 0; }
+
+// n steps from buffer *cur; *cur is then the buffer that they end in.
+hipError_t launch_steps(lbw_batch* b, const lbw::BatchProbeArgs& bp, int64_t n, int* cur, hipStream_t st) {
+    hipError_t e = hipSuccess;
+    for (; n >= 2 && e == hipSuccess && two_steps(b); n -= 2, *cur ^= 1)
+        e = launch_batch2(b, bp, b->f[*cur], b->f[1 - *cur], st);
+    for (; n >= 1 && e == hipSuccess; --n, *cur ^= 1) e = launch_batch(b, bp, b->f[*cur], b->f[1 - *cur], st);
+    return e;
+}
+
+// The segments of two-step launches: each workgroup marches an equal share of
+// the planes of all row tiles, one segment per row tile that it touches; the
+// workgroups of an XCD take consecutive shares.  *ok is false, and nothing is
+// built, where a geometry does not fit, a node is driven, or a segment holds
+// more probes than it records.
+hipError_t build_segments(lbw_batch* b, int cus, bool* ok) {
+    *ok = false;
+    if (b->n_src > 0 || b->n_entries > 0) return hipSuccess;
+    std::vector<int64_t> begin((size_t)b->n + 1, 0);  // planes of all row tiles before a geometry's
+    int threads = 0;
+    for (int h = 0; h < b->n; ++h) {
+        const lbw_geometry_desc& d = b->d[h];
+        const int rows = lbw::batch2_rows(d.n[0], d.n[1]);
+        if (rows == 0 || d.bc_lo[0] == LBW_BC_PERIODIC) return hipSuccess;
+        threads = std::max(threads, lbw::batch2_threads(d.n[0], d.n[1]));
+        begin[(size_t)h + 1] = begin[(size_t)h] + (int64_t)((d.n[1] + rows - 1) / rows) * d.n[2];
+    }
+    const int blocks = std::max(kXcdsBatch, cus / kXcdsBatch * kXcdsBatch);
+    std::vector<lbw::BatchSegment> seg;
+    std::vector<int32_t> first((size_t)blocks + 1, 0);
+    int h = 0;
+    for (int k = 0; k < blocks; ++k) {  // in the order of their shares
+        const int block = k % (blocks / kXcdsBatch) * kXcdsBatch + k / (blocks / kXcdsBatch);
+        int64_t a = 0, e = 0;
+        lbw::march2_share(begin[(size_t)b->n], blocks, block, &a, &e);
+        first[(size_t)k] = (int32_t)seg.size();
+        while (a < e) {
+            while (a >= begin[(size_t)h + 1]) ++h;
+            const int64_t n2 = b->d[h].n[2], in = a - begin[(size_t)h];
+            lbw::BatchSegment s{};
+            s.item = h;
+            s.ty = (int32_t)(in / n2);
+            s.z0 = (int32_t)(in % n2);
+            s.z1 = (int32_t)std::min<int64_t>(n2, s.z0 + (e - a));
+            seg.push_back(s);
+            a += s.z1 - s.z0;
+        }
+    }
+    first[(size_t)blocks] = (int32_t)seg.size();
+    if (b->P > 0) {
+        std::vector<int64_t> probes((size_t)b->P);
+        hipError_t e = hipMemcpyAsync(probes.data(), b->d_nodes, sizeof(int64_t) * b->P, hipMemcpyDeviceToHost,
+                                      b->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+        if (e != hipSuccess) return e;
+        for (const lbw::BatchSegment& s : seg) {
+            const lbw_geometry_desc& d = b->d[s.item];
+            const int rows = lbw::batch2_rows(d.n[0], d.n[1]);
+            int count = 0;
+            for (int64_t p = b->probe_off[s.item]; p < b->probe_off[s.item + 1]; ++p) {
+                const int64_t row = probes[(size_t)p] / d.n[0], y = row % d.n[1], z = row / d.n[1];
+                count += y / rows == s.ty && z >= s.z0 && z < s.z1;
+            }
+            if (count > lbw::march2_tile_probes()) return hipSuccess;
+        }
+    }
+    hipError_t e = hipStreamSynchronize(b->stream);
+    if (e != hipSuccess) return e;
+    (void)hipFree(b->d_seg);
+    (void)hipFree(b->d_seg_begin);
+    b->d_seg = nullptr;
+    b->d_seg_begin = nullptr;
+    e = hipMalloc((void**)&b->d_seg, sizeof(lbw::BatchSegment) * seg.size());
+    if (e == hipSuccess) e = hipMalloc((void**)&b->d_seg_begin, sizeof(int32_t) * first.size());
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b->d_seg, seg.data(), sizeof(lbw::BatchSegment) * seg.size(), hipMemcpyHostToDevice,
+                           b->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b->d_seg_begin, first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice,
+                           b->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);  // host tables go out of scope
+    if (e != hipSuccess) return e;
+    b->blocks2 = blocks;
+    b->threads2 = threads;
+    *ok = true;
+    return hipSuccess;
+}
+
 // Planes per thread with which every geometry fits a workgroup of the
 // many-step kernel (the fewest: the most threads), and no thread drives two
 // nodes; driven: (geometry, node) of the driven nodes, sorted by geometry.
@@ -224,11 +329,7 @@ hipError_t build_graph(lbw_batch* b, int from) {
     e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         int cur = from;
-        hipError_t le = hipSuccess;
-        for (int i = 0; i < b->graph_block && le == hipSuccess; ++i) {
-            le = launch_batch(b, bp, b->f[cur], b->f[1 - cur], cap);
-            cur ^= 1;
-        }
+        const hipError_t le = launch_steps(b, bp, b->graph_block, &cur, cap);
         e = hipStreamEndCapture(cap, &graph);
         if (e == hipSuccess) e = le;
     }
@@ -511,7 +612,7 @@ int lbw_batch_set_step_config(lbw_batch_t b, int tile_x, int chunk_z, int blocks
         return fail(LBW_EINVAL, "tile_x must be 0 (whole cross-sections), 16, 32 or 64");
     if (chunk_z < 1 || blocks < 0) return fail(LBW_EINVAL, "chunk_z must be >= 1 and blocks >= 0");
     const int rc = set_config(b, tile_x, chunk_z, blocks);
-    if (rc == LBW_OK) b->resident = false;  // the shape asked for is that of single steps
+    if (rc == LBW_OK) b->resident = b->two = false;  // the shape asked for is that of single steps
     return rc;
 }
 
@@ -560,17 +661,15 @@ int lbw_batch_step_n(lbw_batch_t b, int64_t n) {
         while (n >= K) {
             if (!b->graph[b->cur]) HIP_TRY(build_graph(b, b->cur), "lbw_batch_step_n: graph capture");
             HIP_TRY(hipGraphLaunch(b->graph[b->cur], b->stream), "lbw_batch_step_n: graph launch");
-            if (K & 1) b->cur ^= 1;
+            if ((two_steps(b) ? K / 2 + K % 2 : K) & 1) b->cur ^= 1;
             b->t += K;
             n -= K;
         }
     }
-    const lbw::BatchProbeArgs bp = probe_args(b, true);
-    for (int64_t i = 0; i < n; ++i) {
-        HIP_TRY(launch_batch(b, bp, b->f[b->cur], b->f[1 - b->cur], b->stream), "lbw_batch_step_n");
-        b->cur ^= 1;
-        b->t += 1;
-    }
+    int cur = b->cur;
+    HIP_TRY(launch_steps(b, probe_args(b, true), n, &cur, b->stream), "lbw_batch_step_n");
+    b->cur = cur;
+    b->t += n;
     return LBW_OK;
 }
 
@@ -640,7 +739,26 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
         if (!(err == hipSuccess && ms < best_ms)) b->nts = policy;
         else best_ms = ms;
     }
-    // many steps per launch against the best single step
+    // two steps per launch against the best single step
+    b->two = false;
+    bool two = false;
+    if (err == hipSuccess) err = build_segments(b, cus, &two);
+    if (err == hipSuccess && two) {
+        float* bufs[2] = {other, tmp};
+        int w = 0;
+        err = launch_batch2(b, bp, b->f[b->cur], other, b->stream);
+        if (err == hipSuccess) err = hipEventRecord(e0, b->stream);
+        for (int r = 0; r < reps && err == hipSuccess; ++r, w ^= 1)
+            err = launch_batch2(b, bp, bufs[w], bufs[w ^ 1], b->stream);
+        if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
+        if (err == hipSuccess) err = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+        ms *= 0.5f;
+        two = err == hipSuccess && ms < best_ms;
+        if (two) best_ms = ms;
+    }
+    // many steps per launch against the best of these
     bool resident = false;
     if (err == hipSuccess && b->run > 0) {
         lbw::BatchProbeArgs rp = bp;
@@ -661,7 +779,11 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
             resident = true;
         }
     }
-    if (err == hipSuccess) b->resident = resident;
+    if (err == hipSuccess) {
+        b->resident = resident;
+        b->two = two;
+        b->plan_version += 1;
+    }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipStreamSynchronize(b->stream);

@@ -150,6 +150,7 @@ struct BatchItem {
     float c2, two_w0, damp;
     int ntx, nty, lz;
     int rty;             // rows per tile when the tiles hold whole rows (run-time tiles)
+    int rty2;            // rows per tile of two-step launches (0: not possible)
     int64_t tile_begin;  // first global tile of this geometry
     int64_t tiles;
     uint64_t f_off;      // float offset of the population block (Q * N floats)
@@ -203,6 +204,20 @@ int batch_section_blocks_per_cu(int nt);
 hipError_t launch_step_batch(const BatchItem* items, const int32_t* tile_item, int n_items, int64_t tiles_total,
                              int tx, int section_nt, int blocks, bool nts, bool pery, const BatchProbeArgs& bp,
                              const float* fin, float* fout, hipStream_t st);
+
+// Two steps of every geometry of a batch per launch (step_march2.hip): tiles of
+// rty2 whole axis-0 rows, walls on axis 0, no driven nodes; workgroup b marches
+// the segments seg_begin[b] .. seg_begin[b + 1], planes [z0, z1) of row tile ty
+// of a geometry, with at most march2_tile_probes() probes each.  The times are
+// read from bank bp.parity and written to the other.
+struct BatchSegment {
+    int32_t item, ty, z0, z1;
+};
+int batch2_rows(int n0, int n1);     // rows per tile of an n0 x n1 cross-section; 0: its rows do not fit
+int batch2_threads(int n0, int n1);  // threads such a tile needs (a launch takes the most of its geometries)
+hipError_t launch_step_batch2(const BatchItem* items, const BatchSegment* seg, const int32_t* seg_begin, int n_items,
+                              int blocks, int threads, bool pery, const BatchProbeArgs& bp, const float* fin,
+                              float* fout, hipStream_t st);
 
 // Up to kResidentSteps steps of every geometry of a batch in one launch, a
 // workgroup per geometry with its state on chip (step_resident.hip).  `run`

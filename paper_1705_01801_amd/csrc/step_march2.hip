@@ -47,26 +47,32 @@ using namespace march;
 
 constexpr int kTileProbes = 16;
 
-template <int TX, int TY>
+// RT: the tile is run-time, whole rows of n0 <= TX columns, as many as fit the
+// threads; TX x TY then only sizes the LDS arrays (kRtSlots bounds the padded
+// tile, checked by the host).
+constexpr int kRtSlots = 1400;
+template <int TX, int TY, bool RT = false>
 struct M2 {
     static constexpr int NT = TX * (TY + 2);
     static constexpr int W = TX + 2;          // LDS row: one pad entry either side of the axis-0 row
-    static constexpr int SROWS = TY + 6;      // S(t) of extended rows -2 .. TY+3
-    static constexpr int XROWS = TY + 4;      // populations handed over by rows -1 .. TY+2
-    static constexpr int S1ROWS = TY + 4;     // S(t+1) of rows -1 .. TY+2 (the outer two unused)
+    static constexpr int S = RT ? kRtSlots : (TY + 6) * W;   // S(t) of extended rows -2 .. TY+3
+    static constexpr int X = RT ? kRtSlots : (TY + 4) * W;   // populations handed over by rows -1 .. TY+2
+    static constexpr int S1 = RT ? kRtSlots : (TY + 4) * W;  // S(t+1) of rows -1 .. TY+2 (the outer two unused)
+    static constexpr int B = RT ? NT : TY * TX;
 };
 
-template <int TX, int TY>
+template <int TX, int TY, bool RT = false>
 struct M2Lds {
-    float S[2][M2<TX, TY>::SROWS * M2<TX, TY>::W + 1];     // + a sink slot
-    float X[4][M2<TX, TY>::XROWS * M2<TX, TY>::W + 1];     // (the last slot takes what nobody reads)
-    float S1[2][M2<TX, TY>::S1ROWS * M2<TX, TY>::W];
+    using C = M2<TX, TY, RT>;
+    float S[2][C::S + 1];      // + a sink slot
+    float X[4][C::X + 1];      // (the last slot takes what nobody reads)
+    float S1[2][C::S1 + 1];
     // coefficient rows, slot = (plane - za0) mod 6: c^2 Mhat00, 02, 22, 11,
     // c^2 Gamh0 / 2, c^2 Gamh2 / 2, an array each (96 x 256 x 512 torus: 104 us
     // per step; with records of 16 bytes, whose ten reads per plane and wave
     // were most of the LDS's time, 120)
-    float E[6][6 * M2<TX, TY>::W + 1];                     // + a sink slot
-    float B[2][2][TY * TX + 1];                            // step B: +-e0 populations along the row (2 planes)
+    float E[6][6 * C::W + 1];  // + a sink slot
+    float B[2][2][C::B + 1];   // step B: +-e0 populations along the row (2 planes)
     int pnode[kTileProbes], px[kTileProbes], py[kTileProbes], pz[kTileProbes];
     int pcount;
 };
@@ -98,21 +104,24 @@ __device__ __forceinline__ void bload7u(__amdgpu_buffer_rsrc_t r, uint32_t N4, u
 
 // PERY, PERZ: axis 1, axis 2 is periodic (every link along it present;
 // the wall rules of that axis are compiled out).
-template <int TX, int TY, bool PERY, bool PERZ>
-__device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& pr, int64_t t, int ty, int z0, int z1,
-                                            const float* __restrict__ fin, float* __restrict__ fout,
-                                            M2Lds<TX, TY>& L) {
-    using C = M2<TX, TY>;
-    constexpr int W = C::W;
+// rows: the tile's rows (RT; else TY); stride: the trace's row length.
+template <int TX, int TY, bool PERY, bool PERZ, bool RT = false>
+__device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& pr, int64_t stride, int64_t t, int ty,
+                                            int rows, int z0, int z1, const float* __restrict__ fin,
+                                            float* __restrict__ fout, M2Lds<TX, TY, RT>& L) {
+    using C = M2<TX, TY, RT>;
+    const int TXr = RT ? g.n0 : TX, TYr = RT ? rows : TY;
+    const int W = TXr + 2;
     const int n0 = g.n0, n1 = g.n1, n2 = g.n2;
     const uint32_t N = (uint32_t)g.N;
     const uint32_t plane = (uint32_t)n0 * (uint32_t)n1;
     const float c2 = g.c2, two_w0 = g.two_w0, damp = g.damp;
-    const int lx = (int)(threadIdx.x % (unsigned)TX), ly = (int)(threadIdx.x / (unsigned)TX);
-    // row tile ty (rows ty TY ..), planes [z0, z1) with 0 <= z0 < z1 <= n2
-    const int y0 = ty * TY;
-    const int hgt = min(TY, n1 - y0);
-    const bool perz = g.bc_lo[2] == LBW_BC_PERIODIC, pery = PERY;
+    const int lx = (int)(threadIdx.x % (unsigned)TXr), ly = (int)(threadIdx.x / (unsigned)TXr);
+    // row tile ty (rows ty TYr ..), planes [z0, z1) with 0 <= z0 < z1 <= n2
+    const int y0 = ty * TYr;
+    const int hgt = min(TYr, n1 - y0);
+    const bool perz = g.bc_lo[2] == LBW_BC_PERIODIC;
+    const bool pery = PERY || (RT && g.bc_lo[1] == LBW_BC_PERIODIC);  // (a batch may mix both)
     // step A runs on march planes [za0, za1); the march runs on [za0, z1 + 2)
     const int za0 = perz ? z0 - 2 : max(z0 - 2, 0);
     const int za1 = perz ? z1 + 2 : min(z1 + 2, n2);
@@ -121,7 +130,8 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     const int yr = y0 - 1 + ly;
     const bool ypres = pery || (yr >= 0 && yr < n1);
     const int ya = pery ? wrap(yr, n1) : yr;
-    const bool actA = lx < n0 && ypres;
+    const bool idle = RT && ly > TYr + 1;  // (threads beyond the halo rows)
+    const bool actA = lx < n0 && ypres && !idle;
     const bool actB = actA && ly >= 1 && ly <= hgt;
     // waves with no lane on the tile's own rows (all in the halo rows) skip
     // step B altogether (it has no barrier; its hand-over slots are read
@@ -139,8 +149,8 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
 
     // ring loader: rows -1 and TY+2 (loaded and collided: they send +e1 / -e1
     // into the halo rows), rows -2 and TY+3 (loaded for S only)
-    const int rid = (int)(threadIdx.x / (unsigned)TX);  // 0..3 for loaders
-    const int re = rid == 0 ? -1 : rid == 1 ? TY + 2 : rid == 2 ? -2 : TY + 3;
+    const int rid = ly;  // 0..3 for loaders
+    const int re = rid == 0 ? -1 : rid == 1 ? TYr + 2 : rid == 2 ? -2 : TYr + 3;
     const int ryr = y0 - 1 + re;
     const bool rpres = rid < 4 && (pery || (ryr >= 0 && ryr < n1));
     const int rya = pery ? wrap(ryr, n1) : ryr;
@@ -151,8 +161,9 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     kr.jy_m = rpres ? link_coord(rya, -1, n1, g.bc_lo[1], g.bc_hi[1], &kr.wy_m) : -1;
     const uint32_t ring4 = ring_on ? ((uint32_t)lx + (uint32_t)n0 * (uint32_t)rya) * 4u : 0u;
     const int my_s = (ly + 2) * W + lx + 1;                  // own S(t) slot
-    const int ring_s = ring_on ? (re + 2) * W + lx + 1 : C::SROWS * W;
+    const int ring_s = ring_on ? (re + 2) * W + lx + 1 : C::S;
     const int xo = my_s - W;                                 // own slot of X and S1
+    const int my_w = idle ? C::S : my_s, xw = idle ? C::X : xo;  // written (idle threads: the sinks)
 
     // The walls of axis 0 as lane constants instead of selections per plane:
     // across a wall a lane reads its own S (negated for a fixed wall) and
@@ -167,11 +178,11 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     const float sg_m = !xm && g.bc_lo[0] == LBW_BC_FIXED ? -1.f : 1.f;
     const float fac1 = xm || free_m ? 1.f : g.bc_lo[0] == LBW_BC_BOUNCEBACK ? damp : -1.f;
     const float fac2 = xp || free_p ? 1.f : g.bc_hi[0] == LBW_BC_BOUNCEBACK ? damp : -1.f;
-    constexpr int XS = C::XROWS * W + 1, BS = TY * TX + 1;
+    constexpr int XS = C::X + 1, BS = C::B + 1;
     const int ix1 = xm ? xo - 1 : free_m ? xo : XS + xo, ix2 = xp ? XS + xo + 1 : free_p ? XS + xo : xo;
-    const int bo = actB ? (ly - 1) * TX + lx : TY * TX;      // step B hand-over slot
-    const int ib1 = !actB ? TY * TX : xm ? bo - 1 : free_m ? bo : BS + bo;
-    const int ib2 = !actB ? TY * TX : xp ? BS + bo + 1 : free_p ? BS + bo : bo;
+    const int bo = actB ? (ly - 1) * TXr + lx : C::B;        // step B hand-over slot
+    const int ib1 = !actB ? C::B : xm ? bo - 1 : free_m ? bo : BS + bo;
+    const int ib2 = !actB ? C::B : xp ? BS + bo + 1 : free_p ? BS + bo : bo;
 
     // lane parts of the offsets in memory
     const uint32_t N4 = N * 4u, plane4 = plane * 4u;
@@ -184,7 +195,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
     const int erec = (int)(threadIdx.x / 6u), ecoef = (int)(threadIdx.x % 6u);
     const bool erow_on = erec < n0;
     const uint32_t erow4 = erow_on ? (uint32_t)(erec * 32 + ecoef * 4) : kOff;
-    const int erow_s = erow_on ? ecoef * W + erec + 1 : 6 * W;
+    const int erow_s = erow_on ? ecoef * W + erec + 1 : 6 * C::W;
 
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(fin, 7u * N4);
     const __amdgpu_buffer_rsrc_t rout = make_rsrc(fout, 7u * N4);
@@ -264,7 +275,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
         L.E[5][erow_s] = e0;  // plane za0 - 1
         L.E[0][erow_s] = e1;
         L.E[1][erow_s] = e2;
-        L.S[0][my_s] = Sc;
+        L.S[0][my_w] = Sc;
         L.S[0][ring_s] = sum7(rA);
     }
     {
@@ -358,22 +369,23 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
             float fs[7];
             collide(fc, Sc, e_lo, e_hi, enp, enm, ezp, make_float2(ezm.y, ezm.z), sg_p * Ls[sxp], sg_m * Ls[sxm],
                     Ls[my_s + W], Ls[my_s - W], Sp, Sm, k, c2, two_w0, fs);
-            L.X[0][xo] = fs[1];
-            L.X[1][xo] = fs[2];
-            L.X[2][xo] = fs[3];
-            L.X[3][xo] = fs[4];
+            L.X[0][xw] = fs[1];
+            L.X[1][xw] = fs[2];
+            L.X[2][xw] = fs[3];
+            L.X[3][xw] = fs[4];
             // the ring rows -1 and TY+2 (threads of the first 2 TX, whole
             // waves) send f*_3 (row -1, into row 0) and f*_4 (row TY+2, into
             // row TY+1): the axis-1 part of their collision
-            // (2 TX is a multiple of 64: whole waves, tested as such)
-            if (__builtin_amdgcn_readfirstlane((int)threadIdx.x) < 2 * TX) {
-                const int ri = (re + 2) * W + lx + 1;
+            // (where 2 TX is no multiple of 64, the last of these waves holds
+            // other lanes too: row -1's slots, and the sink)
+            if (__builtin_amdgcn_readfirstlane((int)threadIdx.x) < 2 * TXr) {
+                const int ri = (RT && rid > 1 ? 1 : re + 2) * W + lx + 1;
                 float rs3, rs4;
                 collide_axis1(rc[3], rc[4], sum7(rc), e_lo.w, Ls[ri + W], Ls[ri - W], krp, c2, rs3, rs4);
                 const int ro = (re + 1) * W + lx + 1;
                 // (row -1 sends f*_3 through X[2], row TY+2 f*_4 through X[3];
                 // one store by index, no branch)
-                (&L.X[0][0])[(rid == 0 ? 2 * XS : 3 * XS) + (ring_col ? ro : C::XROWS * W)] = rid == 0 ? rs3 : rs4;
+                (&L.X[0][0])[(rid == 0 ? 2 * XS : 3 * XS) + (ring_col ? ro : C::X)] = rid == 0 ? rs3 : rs4;
             }
             __syncthreads();  // handed-over populations visible
             f2[0] = fs[0];
@@ -389,7 +401,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
         // plane z-1 is complete: its S(t+1) for step B's neighbours
         if (z - 1 >= za0 && z - 1 < za1) {
             S1c = sum7(f1);
-            L.S1[(K + 1) & 1][xo] = S1c;  // plane z - 1
+            L.S1[(K + 1) & 1][xw] = S1c;  // plane z - 1
         }
 
         // step B on plane zb = z - 2
@@ -414,7 +426,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
                     if (actB && L.pz[i] == zbr && L.py[i] == ya && L.px[i] == lx) {
                         double s = 0.0;
                         for (int l = 0; l < 7; ++l) s += (double)f0[l];
-                        pr.trace[(t + 1) * pr.n + L.pnode[i]] = s / g.sqrtg[lx + (int64_t)n0 * zbr];
+                        pr.trace[(t + 1) * stride + L.pnode[i]] = s / g.sqrtg[lx + (int64_t)n0 * zbr];
                     }
                 }
             }
@@ -445,7 +457,7 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
         // stage S(t) of plane z+1 and the coefficient row z+2 for the next
         // march plane (their slots were last read two barriers ago)
         if (z + 1 < zend) {
-            L.S[sb ^ 1][my_s] = Sp;
+            L.S[sb ^ 1][my_w] = Sp;
             L.S[sb ^ 1][ring_s] = Srp;
             L.E[(K + 2) % 6][erow_s] = en;
         }
@@ -491,7 +503,7 @@ __global__ __launch_bounds__(TX * (TY + 2)) void step_march2_kernel(GeomDev g, P
         const int t_end = (int)(plan.tiles * (xcd + 1) / kXcds);
         for (int tile = t_begin + (int)blockIdx.x / kXcds; tile < t_end; tile += per_xcd_blocks) {
             const int ty = tile % plan.nty, z0 = (tile / plan.nty) * plan.lz;
-            if (z0 < g.n2) march2_tile<TX, TY, PERY, PERZ>(g, pr, t, ty, z0, min(z0 + plan.lz, g.n2), fin, fout, L);
+            if (z0 < g.n2) march2_tile<TX, TY, PERY, PERZ>(g, pr, pr.n, t, ty, TY, z0, min(z0 + plan.lz, g.n2), fin, fout, L);
         }
     } else {
         // balanced: this workgroup's share of the (row tile, plane) pairs,
@@ -501,9 +513,75 @@ __global__ __launch_bounds__(TX * (TY + 2)) void step_march2_kernel(GeomDev g, P
         while (a < e) {
             const int ty = (int)(a / g.n2), z0 = (int)(a % g.n2);
             const int z1 = (int)min((int64_t)g.n2, (int64_t)z0 + (e - a));
-            march2_tile<TX, TY, PERY, PERZ>(g, pr, t, ty, z0, z1, fin, fout, L);
+            march2_tile<TX, TY, PERY, PERZ>(g, pr, pr.n, t, ty, TY, z0, z1, fin, fout, L);
             a += z1 - z0;
         }
+    }
+}
+
+// The geometries of a batch, two steps per launch: row tiles of it.rty2 whole
+// axis-0 rows, marched in the segments that the host dealt out (equal shares of
+// the planes: tiles of 24 planes, the best of fixed lengths, cost 13 us a step
+// more).  96 horns of about 20 x 52 x 184: 169 us per step; single steps, bound by
+// memory at 4.9 TB/s, 203.  Nine waves of a row tile's 28 x 20 threads leave the
+// latency of a plane less hidden than in step_march2_kernel.
+template <bool PERY>
+__global__ __launch_bounds__(768) void step_batch2_kernel(const BatchItem* __restrict__ items,
+                                                          const BatchSegment* __restrict__ seg,
+                                                          const int32_t* __restrict__ seg_begin, int n_items,
+                                                          BatchProbeArgs bp, const float* __restrict__ fin,
+                                                          float* __restrict__ fout) {
+    __shared__ M2Lds<96, 6, true> L;
+    const int64_t* __restrict__ t_now = bp.tcount + (size_t)bp.parity * n_items;
+    const auto geom = [&](const BatchItem& it, GeomDev& g, ProbeArgs& pr) {
+        g.dim = 3;
+        g.n0 = it.n0;
+        g.n1 = it.n1;
+        g.n2 = it.n2;
+        g.N = it.N;
+        for (int a = 0; a < 3; ++a) {
+            g.bc_lo[a] = it.bc_lo[a];
+            g.bc_hi[a] = it.bc_hi[a];
+        }
+        g.c2 = it.c2;
+        g.two_w0 = it.two_w0;
+        g.damp = it.damp;
+        g.tab = reinterpret_cast<const float*>(bp.tab4 + 2 * (size_t)it.tab_off);
+        g.sqrtg = bp.sqrtg + it.sg_off;
+        g.sg_node = 0;
+        pr.nodes = bp.nodes + it.probe_off;
+        pr.n = it.n_probes;
+        pr.trace = bp.trace + it.probe_off;
+        pr.t_max = bp.t_max;
+    };
+    // time t, from the input; the next time into the other bank
+    for (int h = blockIdx.x; h < n_items; h += gridDim.x) {
+        GeomDev g{};
+        ProbeArgs pr{};
+        geom(items[h], g, pr);
+        const int64_t t = t_now[h];
+        if (t >= 0 && t < pr.t_max) {
+            const float* f = fin + items[h].f_off;
+            for (int p = threadIdx.x; p < pr.n; p += blockDim.x) {
+                const uint32_t node = (uint32_t)pr.nodes[p];
+                const uint32_t e = node % (uint32_t)g.n0 + (uint32_t)g.n0 * (node / ((uint32_t)g.n0 * (uint32_t)g.n1));
+                double s = 0.0;
+                for (int l = 0; l < 7; ++l) s += (double)f[(uint32_t)l * (uint32_t)g.N + node];
+                pr.trace[t * bp.stride + p] = s / g.sqrtg[e];
+            }
+        }
+        if (threadIdx.x == 0) bp.tcount[(size_t)(bp.parity ^ 1) * n_items + h] = t + 2;
+    }
+    // the shares of an XCD's workgroups (those equal modulo 8) follow each other
+    const int share = (int)(blockIdx.x % kXcds) * (int)(gridDim.x / kXcds) + (int)(blockIdx.x / kXcds);
+    for (int i = seg_begin[share]; i < seg_begin[share + 1]; ++i) {
+        const BatchSegment sg = seg[i];
+        const BatchItem& it = items[sg.item];
+        GeomDev g{};
+        ProbeArgs pr{};
+        geom(it, g, pr);
+        march2_tile<96, 6, PERY, false, true>(g, pr, bp.stride, t_now[sg.item], sg.ty, it.rty2, sg.z0, sg.z1,
+                                              fin + it.f_off, fout + it.f_off, L);
     }
 }
 
@@ -565,6 +643,38 @@ void launch2_of(bool pery, bool perz, dim3 grid, dim3 block, hipStream_t st, con
         hipLaunchKernelGGL((step_march2_kernel<TX, TY, false, false>), grid, block, 0, st, g, pr, plan, fin, fout);
 }
 }  // namespace
+
+int batch2_rows(int n0, int n1) {
+    // rows with their two halo rows fit the threads, four of them load rings;
+    // equal shares of the axis-1 rows
+    if (n0 < 4 || n0 > 96) return 0;
+    const int most = 768 / n0 - 2;
+    if (most < 2) return 0;
+    const int tiles = (n1 + most - 1) / most, rows = (n1 + tiles - 1) / tiles;
+    // the slots that any thread, idle ones included, reads or writes
+    const int last = 767 / n0 > rows + 3 ? 767 / n0 : rows + 3;
+    return (last + 4) * (n0 + 2) <= kRtSlots ? rows : 0;
+}
+
+int batch2_threads(int n0, int n1) {
+    // the tile with its halo rows, and a coefficient row by one thread a value
+    const int rows = batch2_rows(n0, n1), need = (rows + 2 > 6 ? rows + 2 : 6) * n0;
+    return (need + 63) / 64 * 64;
+}
+
+hipError_t launch_step_batch2(const BatchItem* items, const BatchSegment* seg, const int32_t* seg_begin, int n_items,
+                              int blocks, int threads, bool pery, const BatchProbeArgs& bp, const float* fin,
+                              float* fout, hipStream_t st) {
+    if (blocks < kXcds || blocks % kXcds || threads < 64 || threads > 768) return hipErrorInvalidValue;
+    const dim3 grid(blocks), block(threads);
+    if (pery)
+        hipLaunchKernelGGL((step_batch2_kernel<true>), grid, block, 0, st, items, seg, seg_begin, n_items, bp, fin,
+                           fout);
+    else
+        hipLaunchKernelGGL((step_batch2_kernel<false>), grid, block, 0, st, items, seg, seg_begin, n_items, bp, fin,
+                           fout);
+    return hipGetLastError();
+}
 
 hipError_t launch_step_march2(const GeomDev& g, const ProbeArgs& pr, const MarchPlan& plan, const float* fin,
                               float* fout, hipStream_t st) {
