@@ -85,29 +85,6 @@ constexpr int lds_s() {
     return RT ? 4 * NT + 8 : (NT / TX + 2) * (TX + 2) + 1;
 }
 
-// Coefficient rows of three planes in LDS, entries x0 - 1 .. x0 + TX and a
-// sink slot, one array per coefficient: c^2 Mhat00, 02, 22, 11,
-// c^2 Gamh0 / 2, c^2 Gamh2 / 2.  In tiles narrower than 64 columns a wave holds
-// several rows, whose lanes read the same entries, and the LDS serves equal
-// addresses in one pass only for reads of 4 bytes: a step of a 24 x 48 x 128
-// horn takes 6.2 us, with records of 32 bytes 6.5 (wider tiles: no difference).
-template <int TX>
-struct Rows {
-    float v[3][6][TX + 3];
-    __device__ void put(int slot, int i, const float4& lo, const float4& hi) {
-        v[slot][0][i] = lo.x;
-        v[slot][1][i] = lo.y;
-        v[slot][2][i] = lo.z;
-        v[slot][3][i] = lo.w;
-        v[slot][4][i] = hi.x;
-        v[slot][5][i] = hi.y;
-    }
-    __device__ float4 lo(int slot, int i) const {
-        return make_float4(v[slot][0][i], v[slot][1][i], v[slot][2][i], v[slot][3][i]);
-    }
-    __device__ float4 hi(int slot, int i) const { return make_float4(v[slot][4][i], v[slot][5][i], 0.f, 0.f); }
-};
-
 // One tile of one geometry: columns [x0, x0 + TX) x [y0, y0 + TY), planes
 // [z0, z0 + lz).  fin/fout point at the geometry's own population block.
 // RT: the tile is g.rtx x g.rty columns instead (at most NT of them, with
@@ -122,7 +99,7 @@ template <int TX, int NT, bool ROW, bool RT = false, bool NTS = false, bool SRC 
           bool PERY = false>
 __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const float* __restrict__ fin,
                                            float* __restrict__ fout, float (&sS)[2][lds_s<TX, NT, RT>()],
-                                           Rows<TX>& sE) {
+                                           float4 (&sElo)[3][TX + 3], float4 (&sEhi)[3][TX + 3]) {
     const int TXr = RT ? g.rtx : TX;
     const int TY = RT ? g.rty : NT / TX;
     const int W = TXr + 2;
@@ -242,10 +219,12 @@ __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const fl
             em = make_float2(e.y, e.z);
             Sc = sum7(fc);
             if (e0_on) {
-                sE.put(0, threadIdx.x, a0, b0);
+                sElo[0][threadIdx.x] = a0;
+                sEhi[0][threadIdx.x] = b0;
             }
             if (e1_on) {
-                sE.put(1, threadIdx.x, a1, b1);
+                sElo[1][threadIdx.x] = a1;
+                sEhi[1][threadIdx.x] = b1;
             }
             if (ring_on) sS[0][ring_lds] = sum7(rz);
             if (active) sS[0][my_lds] = Sc;
@@ -301,8 +280,8 @@ __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const fl
 
             const float* L = sS[sb];
             const float S = Sc;
-            const float4 e_lo = sE.lo(es, lx + 1);  // 00, 02, 22, 11
-            const float4 e_hi = sE.hi(es, lx + 1);  // g0/2, g2/2, 0, 0
+            const float4 e_lo = sElo[es][lx + 1];  // 00, 02, 22, 11
+            const float4 e_hi = sEhi[es][lx + 1];  // g0/2, g2/2, 0, 0
             // axis-0/1 neighbours: read unconditionally (every index is inside
             // the LDS arrays); collide() selects the wall rule
             Links k;
@@ -319,7 +298,7 @@ __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const fl
             k.wz_p = wz_p;
             k.wz_m = wz_m;
             float fs[7];
-            collide(fc, S, e_lo, e_hi, sE.lo(es, lx + 2), sE.lo(es, lx), sE.lo(es1, lx + 1), em, L[my_lds + 1],
+            collide(fc, S, e_lo, e_hi, sElo[es][lx + 2], sElo[es][lx], sElo[es1][lx + 1], em, L[my_lds + 1],
                     L[my_lds - 1], L[my_lds + W], L[my_lds - W], Sp, Sm, k, c2, two_w0, fs);
             const float cM02 = e_lo.y, cM22 = e_lo.z;
 
@@ -382,7 +361,8 @@ __device__ __forceinline__ void march_tile(const TileGeom& g, int tile, const fl
                 drive_loaded<SRC>(g, jz_p, ring_on, ring_col, r1);
                 // disabled lanes write the sink slot past the end (never read)
                 sS[sb ^ 1][ring_on ? ring_lds : kSinkS] = sum7(r1);
-                sE.put(es2, e_on ? (int)threadIdx.x : TXr + 2, e1[0], e1[1]);
+                sElo[es2][e_on ? (int)threadIdx.x : TXr + 2] = e1[0];
+                sEhi[es2][e_on ? (int)threadIdx.x : TXr + 2] = e1[1];
                 sS[sb ^ 1][active ? my_lds : kSinkS] = Sp;
                 Sm = Sc;
                 Sc = Sp;
@@ -407,7 +387,8 @@ __global__ __launch_bounds__(NT) void step_march_kernel(GeomDev g, ProbeArgs pr,
                                                               const float* __restrict__ fin,
                                                               float* __restrict__ fout) {
     __shared__ float sS[2][lds_s<TX, NT, false>()];
-    __shared__ Rows<TX> sE;
+    __shared__ float4 sElo[3][TX + 3];
+    __shared__ float4 sEhi[3][TX + 3];
     if (blockIdx.x == 0) record_probes<7>(g, pr, 1, fin);
     TileGeom tg;
     tg.n0 = g.n0;
@@ -434,7 +415,7 @@ __global__ __launch_bounds__(NT) void step_march_kernel(GeomDev g, ProbeArgs pr,
     const int t_begin = (int)(plan.tiles * xcd / kXcds);
     const int t_end = (int)(plan.tiles * (xcd + 1) / kXcds);
     for (int tile = t_begin + (int)blockIdx.x / kXcds; tile < t_end; tile += per_xcd_blocks)
-        march_tile<TX, NT, ROW, false, NTS, false, NTS, PERY>(tg, tile, fin, fout, sS, sE);
+        march_tile<TX, NT, ROW, false, NTS, false, NTS, PERY>(tg, tile, fin, fout, sS, sElo, sEhi);
 }
 
 // Batch of geometries advanced by one launch: tiles of all geometries form
@@ -451,7 +432,8 @@ __global__ __launch_bounds__(NT) void step_batch_kernel(const BatchItem* __restr
                                                          int64_t tiles_total, BatchProbeArgs bp,
                                                          const float* __restrict__ fin, float* __restrict__ fout) {
     __shared__ float sS[2][lds_s<TX, NT, SECTION>()];
-    __shared__ Rows<TX> sE;
+    __shared__ float4 sElo[3][TX + 3];
+    __shared__ float4 sEhi[3][TX + 3];
     // this launch's time per geometry: bank `parity`, which no block of it
     // writes (the probe blocks below write the other bank)
     const int64_t* __restrict__ t_now = bp.tcount + (size_t)bp.parity * n_items;
@@ -521,7 +503,7 @@ __global__ __launch_bounds__(NT) void step_batch_kernel(const BatchItem* __restr
         tg.src_zhi = it.src_zhi;
         tg.src_t = t_now[h];
         march_tile<TX, NT, true, SECTION, NTS, true, false, PERY>(tg, (int)(tile - it.tile_begin), fin + it.f_off,
-                                                     fout + it.f_off, sS, sE);
+                                                     fout + it.f_off, sS, sElo, sEhi);
     }
 }
 
@@ -680,19 +662,21 @@ hipError_t launch_step_batch(const BatchItem* items, const int32_t* tile_item, i
 // One step per launch: a launch costs 3.5; a round of workgroups 1 + 0.85 lz
 // (a plane of the march is a round trip to the caches, so small grids want
 // short chunks on many workgroups); the traffic `node` per million nodes and
-// `lane` per million lanes, with 0.8 / lz more for the two boundary planes of
-// a chunk and up to a quarter more for the workgroups that the last round
-// leaves idle.  Grids in the Infinity Cache pay for lanes, those beyond it for
-// the rows: whole-row tiles store aligned, and rows of whole 128-byte lines
-// cost 3.5 less per million nodes.
-// Two steps per launch (balanced shares): 4, and per plane of the longest
-// share 0.4 + 0.010 n0 (tiles of 96) or 0.65 + 0.004 n0 (128).
+// `lane` per million lanes, with 0.8 / lz (in the cache 0.55 / lz) more for the
+// two boundary planes of a chunk and up to a quarter more for the workgroups
+// that the last round leaves idle.  Grids in the Infinity Cache pay for lanes,
+// those beyond it for the rows: whole-row tiles store aligned, and rows of whole
+// 128-byte lines cost 3.5 less per million nodes.
+// Two steps per launch (balanced shares): 4.5, and per plane of the longest
+// share 0.75 + 0.003 n0 (tiles of 96) or 0.65 + 0.003 n0 (128).
 // The constants are fits to sweeps of every shape over 15 grids.  Measured
 // (32 or 64 wide tiles and chunks of 16, as before, in brackets): horn 24 x 48 x
 // 128 6.1 us (17.1), torus 37 x 61 x 113 8.2 (18.1), box 30 x 200 x 512 36.6
-// (38.5), cylinder 65 x 141 x 311 38.5 (43.5), box 200^3 151 (176), torus 60 x
-// 200 x 400 60.9 with two steps per launch (75.1), horn 91 x 220 x 390 89.8
-// (201), horn 120 x 250 x 400 120.8 (221).
+// (38.5), cylinder 65 x 141 x 311 38.5 (43.5), box 200^3 151 (176); with two
+// steps per launch torus 60 x 200 x 400 58 (75.1), horn 91 x 220 x 390 78 (201),
+// horn 120 x 250 x 400 113 (221); horn 90 x 128 x 256 31.1 (one step 33.9), 96 x
+// 200 x 200 35.2 (41.7), where one step stays 80^3 10.9 (two 13.8) and 48 x 96 x
+// 256 16.6 (21.7).
 void choose_march_plans(const GeomDev& g, int cus, MarchPlan* one, MarchPlan* two, bool* use2) {
     const double M = 1e-6, nodes = M * (double)g.N;
     const bool hbm = march_nts_default(g), walled0 = g.bc_lo[0] != LBW_BC_PERIODIC;
@@ -721,7 +705,7 @@ void choose_march_plans(const GeomDev& g, int cus, MarchPlan* one, MarchPlan* tw
             const double rounds = (double)((p.tiles + slots - 1) / slots);
             const double idle = 1.0 - (double)p.tiles / (rounds * slots);
             const double march = rounds * (1.0 + 0.85 * lz);
-            const double flow = work * (1.0 + 0.8 / lz) * (1.0 + 0.25 * idle / ((1.0 - idle) * rounds));
+            const double flow = work * (1.0 + (hbm ? 0.8 : 0.55) / lz) * (1.0 + 0.25 * idle / ((1.0 - idle) * rounds));
             const double cost = 3.5 + (march > flow ? march : flow);
             if (cost < best) {
                 best = cost;
@@ -735,7 +719,7 @@ void choose_march_plans(const GeomDev& g, int cus, MarchPlan* one, MarchPlan* tw
         if (!march2_fits(g, tx)) continue;
         const MarchPlan p = make_march2_plan(g, tx, ty, 0, cus * march2_blocks_per_cu(tx, ty));
         const double share = (double)p.tiles / (double)p.blocks;
-        const double cost = 4.0 + (tx == 96 ? 0.4 + 0.010 * g.n0 : 0.65 + 0.004 * g.n0) * (share + 5.0);
+        const double cost = 4.5 + (tx == 96 ? 0.75 + 0.003 * g.n0 : 0.65 + 0.003 * g.n0) * (share + 5.0);
         if (cost < best) {
             best = cost;
             *two = p;
