@@ -257,6 +257,13 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
 
     __syncthreads();  // the tile's probe list complete
     const int tile_probes = __builtin_amdgcn_readfirstlane(min(L.pcount, kTileProbes));
+    // the plane of the thread's probe (-1: none in its column; -2: several,
+    // looked up on every plane), so that a plane costs one comparison: with the
+    // list walked on every plane a batch of 96 horns with 8 probes each took 190
+    // us per step instead of 173
+    int probe_z = -1;
+    for (int i = 0; i < tile_probes; ++i)
+        if (actB && L.py[i] == ya && L.px[i] == lx) probe_z = probe_z == -1 ? L.pz[i] : -2;
 
     // ---- prologue: planes za0 - 1 (S only) and za0 (own column, ring,
     // staged S); coefficient rows za0 - 1 .. za0 + 1; in flight into the
@@ -421,9 +428,10 @@ __device__ __forceinline__ void march2_tile(const GeomDev& g, const ProbeArgs& p
             collide(f0, S1b, e_lo, e_hi, enp, enm, ezp, make_float2(ezm.y, ezm.z), sg_p * L1[sxp - W],
                     sg_m * L1[sxm - W], L1[xo + W], L1[xo - W], S1c, S1a, k, c2, two_w0, fs);
             // probes at t+1 on this plane (the state f0 before step B)
-            if (tile_probes > 0) {
+            const bool probed = probe_z == zbr || probe_z == -2;
+            if (__builtin_amdgcn_ballot_w64(probed) != 0) {
                 for (int i = 0; i < tile_probes; ++i) {
-                    if (actB && L.pz[i] == zbr && L.py[i] == ya && L.px[i] == lx) {
+                    if (probed && L.pz[i] == zbr && L.py[i] == ya && L.px[i] == lx) {
                         double s = 0.0;
                         for (int l = 0; l < 7; ++l) s += (double)f0[l];
                         pr.trace[(t + 1) * stride + L.pnode[i]] = s / g.sqrtg[lx + (int64_t)n0 * zbr];
@@ -522,7 +530,7 @@ __global__ __launch_bounds__(TX * (TY + 2)) void step_march2_kernel(GeomDev g, P
 // The geometries of a batch, two steps per launch: row tiles of it.rty2 whole
 // axis-0 rows, marched in the segments that the host dealt out (equal shares of
 // the planes: tiles of 24 planes, the best of fixed lengths, cost 13 us a step
-// more).  96 horns of about 20 x 52 x 184: 169 us per step; single steps, bound by
+// more).  96 horns of about 20 x 52 x 184: 173 us per step; single steps, bound by
 // memory at 4.9 TB/s, 203.  Nine waves of a row tile's 28 x 20 threads leave the
 // latency of a plane less hidden than in step_march2_kernel.
 template <bool PERY>
