@@ -200,11 +200,15 @@ hipError_t launch_batch2(lbw_batch* b, lbw::BatchProbeArgs bp, const float* fin,
 
 bool two_steps(const lbw_batch* b) { return b->two && b->n_src == 0 && b->n_entries == 0; }
 
-// n steps from buffer *cur; *cur is then the buffer that they end in.
+// n steps from buffer *cur; *cur is then the buffer that they end in, that of
+// single steps (two-step launches come in pairs, so four steps return to the
+// buffer that they started from, captured and replayed ones too).
 hipError_t launch_steps(lbw_batch* b, const lbw::BatchProbeArgs& bp, int64_t n, int* cur, hipStream_t st) {
     hipError_t e = hipSuccess;
-    for (; n >= 2 && e == hipSuccess && two_steps(b); n -= 2, *cur ^= 1)
+    for (; n >= 4 && e == hipSuccess && two_steps(b); n -= 4) {
         e = launch_batch2(b, bp, b->f[*cur], b->f[1 - *cur], st);
+        if (e == hipSuccess) e = launch_batch2(b, bp, b->f[1 - *cur], b->f[*cur], st);
+    }
     for (; n >= 1 && e == hipSuccess; --n, *cur ^= 1) e = launch_batch(b, bp, b->f[*cur], b->f[1 - *cur], st);
     return e;
 }
@@ -661,7 +665,7 @@ int lbw_batch_step_n(lbw_batch_t b, int64_t n) {
         while (n >= K) {
             if (!b->graph[b->cur]) HIP_TRY(build_graph(b, b->cur), "lbw_batch_step_n: graph capture");
             HIP_TRY(hipGraphLaunch(b->graph[b->cur], b->stream), "lbw_batch_step_n: graph launch");
-            if ((two_steps(b) ? K / 2 + K % 2 : K) & 1) b->cur ^= 1;
+            if (K & 1) b->cur ^= 1;
             b->t += K;
             n -= K;
         }

@@ -49,7 +49,7 @@ def test_tuned_batch_equals_single_steps(name):
             b.set_step_config(16, 8)
         for k in (1, 2, 32, 33, 7):  # (33: a graph block and a step more)
             b.step(k)
-        b.set_graph_block(5)  # an odd block: two launches of two steps and one of one
+        b.set_graph_block(5)  # an odd block: two launches of two steps and one single
         b.step(31)
         got.append(([b.populations(h).clone() for h in range(len(geoms))], b.probe().copy()))
     for a, c in zip(*[f for f, _ in got]):
