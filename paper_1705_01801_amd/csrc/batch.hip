@@ -1,4 +1,4 @@
-// C-ABI for batches of D3Q7 geometries advanced by one launch per step.
+// C-ABI for batches of D3Q7 geometries: one, two or up to 32 steps of all of them per launch.
 #include <algorithm>
 #include <cmath>
 #include <map>
