@@ -184,7 +184,8 @@ int lbw_get_step_config(lbw_geometry_t g, int* tile_x, int* tile_y, int* chunk_z
  * pairs per workgroup (no workgroup marches two whole chunks while another
  * idles); blocks as in lbw_set_step_config (0 = one wave).  Needs a
  * 3-D built-in geometry with n0 <= tile_x and a walled axis 0.
- * lbw_step_n then runs pairs of steps this way (an odd last step, and
+ * lbw_step_n then runs pairs of steps this way, or four steps at a time where
+ * a new geometry's rule chose them (an odd last step, and
  * states with driven sources or with more than 16 probes in one tile of
  * the pass, use one-step launches).  tile_x = 0 turns it off;
  * lbw_set_step_config also turns it off; lbw_autotune turns it on when
@@ -214,7 +215,10 @@ int lbw_init(lbw_geometry_t g, const double* p0, float* f_a, float* f_b, const i
 
 /* Queues n time steps (BGK, tau = 1/2, fused collide-and-push-stream with
  * walls; Sec. II evolution equation with the Sec. III equilibrium and
- * forcing) and the probe recording; returns without waiting.
+ * forcing) and the probe recording; returns without waiting.  However many
+ * steps a launch takes, the state ends in the buffer that n single steps would
+ * leave it in, except with the two-step launches of lbw_set_step2_config and
+ * lbw_autotune, of which each goes from one buffer to the other.
  * Errors: LBW_EINVAL for n < 0, LBW_EDEVICE on a launch failure. */
 int lbw_step_n(lbw_state_t s, int64_t n);
 

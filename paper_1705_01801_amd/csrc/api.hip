@@ -30,6 +30,7 @@ struct lbw_geometry {
     lbw::MarchPlan plan2{}; // launch shape of the two-step pass, used when use2
     lbw::Tile2Plan tile2{}; // several steps per launch of a 2-D grid
     bool use2 = false;
+    bool use2_rule = false; // use2 by the rule on the grid, neither asked for nor tuned
     int plan_version = 0;   // bumped on every change of plan
 };
 
@@ -237,13 +238,14 @@ int lbw_make_geometry(const lbw_geometry_desc* desc, void* stream, lbw_geometry_
     if (d.dim == 2) g->tile2 = lbw::make_tile2_plan(v, cus);
     if (d.dim == 3) {
         lbw::choose_march_plans(v, cus, &g->plan, &g->plan2, &g->use2);
+        g->use2_rule = g->use2;
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(std::make_tuple(v.n0, v.n1, v.n2));
         if (it != g_tuned.end()) {
             const Tuned& c = it->second;
             g->plan = lbw::make_march_plan(v, c.tx, c.ty, c.lz, c.blocks);
             g->plan.nts = c.nts;
-            g->use2 = false;
+            g->use2 = g->use2_rule = false;
             if (c.tx2 > 0 && lbw::march2_fits(v, c.tx2)) {
                 g->plan2 = lbw::make_march2_plan(v, c.tx2, c.ty2, c.lz2, c.blocks2);
                 g->use2 = true;
@@ -417,7 +419,7 @@ int lbw_set_step_config(lbw_geometry_t g, int tile_x, int tile_y, int chunk_z, i
         blocks = cus * lbw::march_blocks_per_cu(tile_x, tile_y);
     }
     g->plan = lbw::make_march_plan(g->dev, tile_x, tile_y, chunk_z, blocks);
-    g->use2 = false;
+    g->use2 = g->use2_rule = false;
     g->plan_version += 1;
     return LBW_OK;
 }
@@ -425,7 +427,7 @@ int lbw_set_step_config(lbw_geometry_t g, int tile_x, int tile_y, int chunk_z, i
 int lbw_set_step2_config(lbw_geometry_t g, int tile_x, int tile_y, int chunk_z, int blocks) {
     if (!g) return fail(LBW_EINVAL, "geometry is NULL");
     if (tile_x == 0) {
-        g->use2 = false;
+        g->use2 = g->use2_rule = false;
         g->plan_version += 1;
         return LBW_OK;
     }
@@ -443,6 +445,7 @@ int lbw_set_step2_config(lbw_geometry_t g, int tile_x, int tile_y, int chunk_z, 
     }
     g->plan2 = lbw::make_march2_plan(g->dev, tile_x, tile_y, chunk_z, blocks);
     g->use2 = true;
+    g->use2_rule = false;
     g->plan_version += 1;
     return LBW_OK;
 }
@@ -583,10 +586,9 @@ void drop_graphs(lbw_state* s) {
     }
 }
 
-// Captures graph_block steps (one-step launches, or graph_block / 2
-// two-step launches when two) starting from buffer `from` on a private
-// stream (capture only records; nothing runs there).
-hipError_t build_graph(lbw_state* s, int from, bool two) {
+// Captures `launches` launches (of one step, or two when two) starting from
+// buffer `from` on a private stream (capture only records; nothing runs there).
+hipError_t build_graph(lbw_state* s, int from, bool two, int launches) {
     hipStream_t cap = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
     if (e != hipSuccess) return e;
@@ -595,7 +597,6 @@ hipError_t build_graph(lbw_state* s, int from, bool two) {
     if (e == hipSuccess) {
         int cur = from;
         hipError_t le = hipSuccess;
-        const int launches = two ? s->graph_block / 2 : s->graph_block;
         for (int i = 0; i < launches && le == hipSuccess; ++i) {
             le = two ? launch_two(s, cur, cap) : launch_one(s, cur, cap);
             cur ^= 1;
@@ -616,21 +617,33 @@ int lbw_step_n(lbw_state_t s, int64_t n) {
     if (n < 0) return fail(LBW_EINVAL, "negative step count");
     if (n > 1 && tile2_ok(s)) {
         // a launch of several steps takes longer than queueing the next one,
-        // so these are launched directly, not through captured blocks
-        while (n > 0) {
-            const int k = (int)std::min<int64_t>(n, s->g->tile2.k);
-            HIP_TRY(lbw::launch_step_tile2(s->g->dev, probe_args(s, s->cur), s->g->tile2, k, s->f[s->cur],
-                                           s->f[1 - s->cur], s->stream),
-                    "lbw_step_n");
-            s->cur ^= 1;
-            s->t += k;
-            n -= k;
+        // so these are launched directly, not through captured blocks.  The
+        // launches are even or odd in number as the steps are, so that the
+        // state ends in the buffer of single steps (an even number of steps
+        // captured by a caller can be replayed); where that takes as many
+        // launches as steps, single steps follow below.
+        const int64_t k = s->g->tile2.k;
+        int64_t launches = (n + k - 1) / k;
+        launches += (launches ^ n) & 1;
+        if (launches < n) {
+            for (; launches > 0; --launches) {
+                const int steps = (int)((n + launches - 1) / launches);
+                HIP_TRY(lbw::launch_step_tile2(s->g->dev, probe_args(s, s->cur), s->g->tile2, steps, s->f[s->cur],
+                                               s->f[1 - s->cur], s->stream),
+                        "lbw_step_n");
+                s->cur ^= 1;
+                s->t += steps;
+                n -= steps;
+            }
+            return LBW_OK;
         }
-        return LBW_OK;
     }
     const bool two = two_step_ok(s);
-    // steps per captured block: even for two-step launches
-    const int K = two ? s->graph_block & ~1 : s->graph_block;
+    // two-step launches that nobody asked for come in pairs, so that four
+    // steps end in the buffer they started from, as four single steps do
+    const int unit = !two ? 1 : s->g->use2_rule ? 4 : 2;
+    // steps per captured block: whole units
+    const int K = s->graph_block / unit * unit;
     if (K > 0 && n >= K) {
         if (s->graph_version != s->g->plan_version || s->graph_two != two) {
             drop_graphs(s);
@@ -639,19 +652,19 @@ int lbw_step_n(lbw_state_t s, int64_t n) {
         }
         const int launches = two ? K / 2 : K;
         while (n >= K) {
-            if (!s->graph[s->cur]) HIP_TRY(build_graph(s, s->cur, two), "lbw_step_n: graph capture");
+            if (!s->graph[s->cur]) HIP_TRY(build_graph(s, s->cur, two, launches), "lbw_step_n: graph capture");
             HIP_TRY(hipGraphLaunch(s->graph[s->cur], s->stream), "lbw_step_n: graph launch");
             if (launches & 1) s->cur ^= 1;
             s->t += K;
             n -= K;
         }
     }
-    while (two && n >= 2) {
-        HIP_TRY(launch_two(s, s->cur, s->stream), "lbw_step_n");
-        s->cur ^= 1;
-        s->t += 2;
-        n -= 2;
-    }
+    for (; two && n >= unit; n -= unit)
+        for (int i = 0; i < unit; i += 2) {
+            HIP_TRY(launch_two(s, s->cur, s->stream), "lbw_step_n");
+            s->cur ^= 1;
+            s->t += 2;
+        }
     for (int64_t i = 0; i < n; ++i) {
         HIP_TRY(launch_one(s, s->cur, s->stream), "lbw_step_n");
         s->cur ^= 1;
@@ -829,6 +842,7 @@ int lbw_autotune(lbw_state_t s, int reps, double* best_us) {
     g->plan = err == hipSuccess ? best : keep;
     const bool two = err == hipSuccess && best2_ms < 2.f * best_ms;
     g->use2 = two;
+    g->use2_rule = false;
     if (two) g->plan2 = best2;
     g->plan_version += 1;
     if (err != hipSuccess) return hip_fail(err, "lbw_autotune");
