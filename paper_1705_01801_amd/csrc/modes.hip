@@ -52,6 +52,7 @@ constexpr int kMaxLog = 13;      // longest line held in LDS: 8192 points
 constexpr int kRowTile = 256;    // trace rows per block of the transpose
 constexpr int kColTile = 16;     // trace columns per block of the transpose
 constexpr int kPairBlock = 4;    // pairs whose power one block of rows_kernel adds up
+constexpr int kMostPairs = 65532;  // pairs of a chunk: the grid's limit, in whole blocks
 constexpr int kTileK1 = 64, kTileK2 = 16;  // bins per block of the power kernel
 
 // Transform of one length: n = n1 n2.
@@ -672,17 +673,20 @@ int64_t spectra_kept(const Split& sp) {
 }
 
 // Whole groups [g0, g1) of one chunk: at most the columns of one spectrum
-// and, with more than one group, at most kCacheBytes of transforms.
+// and, with more than one group, at most kCacheBytes of transforms.  A group of
+// more than kMostPairs pairs is a chunk for every so many of them (part of
+// `parts`), whose powers are added up in the order of the pairs.
 struct Chunk {
-    int g0, g1, cols, pairs, blocks;
+    int g0, g1, cols, pairs, blocks, part, parts;
 };
 Chunk next_chunk(const Split& sp, const int* group_ncols, int groups, int g0, int cap) {
-    Chunk c{g0, g0, 0, 0, 0};
+    Chunk c{g0, g0, 0, 0, 0, 0, 1};
     while (c.g1 < groups) {
         const int n = group_ncols[c.g1], pairs = c.pairs + pairs_of(n);
         if (c.cols + n > cap) break;
         if (c.g1 > g0 && (size_t)pairs * (size_t)sp.n * sizeof(double2) > kCacheBytes) break;
-        if (pairs > 65535 || c.g1 - g0 >= std::min<int64_t>(65535, spectra_kept(sp))) break;  // grid limit
+        if (pairs > kMostPairs && c.g1 > g0) break;
+        if (c.g1 - g0 >= std::min<int64_t>(65535, spectra_kept(sp))) break;  // grid limit
         c.cols += n;
         c.pairs = pairs;
         c.blocks += blocks_of(n);
@@ -754,12 +758,23 @@ Plan plan_chunks(const Split& sp, const int* group_ncols, int groups, int cap) {
             p.ok = false;
             break;
         }
+        g0 = c.g1;
+        if (c.pairs > kMostPairs) {  // (one group)
+            const int parts = (c.pairs + kMostPairs - 1) / kMostPairs;
+            for (int i = 0; i < parts; ++i) {
+                const int cols = std::min(2 * kMostPairs, c.cols - i * 2 * kMostPairs);
+                p.chunks.push_back(Chunk{c.g0, c.g1, cols, pairs_of(cols), blocks_of(cols), i, parts});
+            }
+            p.cols = std::max<int64_t>(p.cols, 2 * kMostPairs);
+            p.pairs = std::max<int64_t>(p.pairs, kMostPairs);
+            p.blocks = std::max<int64_t>(p.blocks, kMostPairs / kPairBlock);
+            continue;
+        }
         p.chunks.push_back(c);
         p.cols = std::max<int64_t>(p.cols, c.cols);
         p.pairs = std::max<int64_t>(p.pairs, c.pairs);
         p.blocks = std::max<int64_t>(p.blocks, c.blocks);
         p.list += c.pairs + c.blocks + (c.g1 - c.g0);
-        g0 = c.g1;
     }
     p.groups = std::min<int64_t>(groups, std::min<int64_t>(65535, spectra_kept(sp)));
     return p;
@@ -791,6 +806,7 @@ hipError_t launch_modes_grouped(const double* trace, int64_t T, int64_t stride, 
     if (!uniform) {
         list.reserve((size_t)plan.list);
         for (const Chunk& c : plan.chunks) {
+            if (c.parts > 1) continue;
             int col = 0, pair = 0, block = 0;
             for (int g = c.g0; g < c.g1; col += group_ncols[g++])
                 for (int q = 0; q < group_ncols[g]; q += 2)
@@ -809,8 +825,8 @@ hipError_t launch_modes_grouped(const double* trace, int64_t T, int64_t stride, 
     int kept0 = 0;  // first group whose spectrum is kept
     for (size_t i = 0; i < plan.chunks.size(); ++i) {
         const Chunk& c = plan.chunks[i];
-        Groups g = one_group(group_ncols[0]);
-        if (!uniform) {
+        Groups g = one_group(c.parts > 1 ? c.cols : group_ncols[0]);
+        if (!uniform && c.parts == 1) {
             g.cpg = 0;
             g.pair = next;
             g.block = g.pair + c.pairs;
@@ -818,7 +834,7 @@ hipError_t launch_modes_grouped(const double* trace, int64_t T, int64_t stride, 
             next = g.group + (c.g1 - c.g0);
         }
         if (c.cols > 0) launch_transforms(sp, g, w, trace, stride, col0, c.cols, c.pairs, c.blocks, 0, st);
-        launch_power(sp, g, w, c.g0 - kept0, c.g1 - c.g0, 0, st);
+        launch_power(sp, g, w, c.g0 - kept0, c.g1 - c.g0, c.part > 0 ? 1 : 0, st);
         if (i + 1 == plan.chunks.size() || plan.chunks[i + 1].g1 - kept0 > plan.groups) {
             hipLaunchKernelGGL(peaks_kernel, dim3(c.g1 - kept0), dim3(kPeakBlock), 0, st, w.P, w.pmax, w.nmax, sp.n, k,
                                freq + (size_t)kept0 * k, power + (size_t)kept0 * k);
