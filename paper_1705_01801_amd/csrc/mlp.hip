@@ -1046,7 +1046,20 @@ int lbw_mlp_forward(lbw_mlp_t M, const float* x, int B, float* y) {
     if (!M || !x || !y) return fail(LBW_EINVAL, "NULL argument");
     if (B < 1 || B > M->max_batch) return fail(LBW_EINVAL, "batch %d outside [1, %d]", B, M->max_batch);
     if (M->few) {
-        HIP_TRY(few_forward(M, x, B, y), "lbw_mlp_forward");
+        // the rows of x are read while other rows of y are written: where the
+        // two overlap, the narrower goes through the workspace of a training
+        // step (two bytes for each input and output, and more)
+        const size_t nx = sizeof(float) * (size_t)B * M->w[0], ny = sizeof(float) * (size_t)B * M->w[M->L];
+        const uintptr_t x0 = (uintptr_t)x, y0 = (uintptr_t)y;
+        const bool overlap = x0 < y0 + ny && y0 < x0 + nx;
+        float* const work = reinterpret_cast<float*>(M->tr);
+        if (overlap && nx <= ny) {
+            HIP_TRY(hipMemcpyAsync(work, x, nx, hipMemcpyDeviceToDevice, M->stream), "lbw_mlp_forward");
+            x = work;
+        }
+        HIP_TRY(few_forward(M, x, B, overlap && x != work ? work : y), "lbw_mlp_forward");
+        if (overlap && x != work)
+            HIP_TRY(hipMemcpyAsync(y, work, ny, hipMemcpyDeviceToDevice, M->stream), "lbw_mlp_forward");
         return LBW_OK;
     }
     HIP_TRY(cast_input(M, x, B, M->stream), "lbw_mlp_forward");
