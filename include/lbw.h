@@ -377,6 +377,18 @@ int lbw_batch_layout(lbw_batch_t b, int64_t* node_offsets, int64_t* probe_offset
  * workgroups).  lbw_batch_autotune times the candidates instead. */
 int lbw_batch_set_step_config(lbw_batch_t b, int tile_x, int chunk_z, int blocks);
 int lbw_batch_get_step_config(lbw_batch_t b, int* tile_x, int* chunk_z, int* blocks);
+
+/* Steps per launch of lbw_batch_step_n: 1, with the shape above; 2, for
+ * geometries with walls on axis 0, 4 <= n0 <= 96, no driven nodes and at most
+ * 16 probes in any of the equal shares of planes that the workgroups march; or
+ * 32, at most so many, with every geometry held on chip by a workgroup of its
+ * own, for geometries that fit one (lbw_batch_step_n says which).  The results,
+ * and the buffer that holds them, do not depend on it.  The getter gives what
+ * is in use, and for 32 the planes per thread (else 0).
+ * Errors: LBW_EINVAL (another number, a batch it does not fit), LBW_ENOMEM,
+ * LBW_EDEVICE. */
+int lbw_batch_set_steps_per_launch(lbw_batch_t b, int steps);
+int lbw_batch_get_steps_per_launch(lbw_batch_t b, int* steps, int* planes);
 /* Times launch shapes (whole-row tiles when the batch allows them, tile_x
  * 16, 32 and 64; chunk_z 4, 8, 16, 32, 64 and, per tile kind, the four
  * other lengths in 4..64 whose tile count spreads best over the resident
@@ -393,10 +405,14 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us);
 int lbw_batch_set_graph_block(lbw_batch_t b, int steps);
 
 /* Queues n steps of every geometry (probes recorded) without waiting.  Where
- * every geometry is small (at most 768 threads of 16 planes of one column
- * each, 32 probes, 32 driven nodes), up to 32 steps are one launch, unless
+ * every geometry is small, up to 32 steps are one launch, unless
  * lbw_batch_set_step_config asked for a shape of single steps; the results,
- * and the buffer that holds them, are the same. */
+ * and the buffer that holds them, are the same.  Small: with one number R of
+ * planes, 2 to 16, for all geometries of the batch, each needs at most 768
+ * threads, one for every column and run of R or R - 1 planes (so
+ * n2 >= ceil(n2 / R) (R - 1)); (n0 + 2) (n2 + 4) <= 2816; at most 32 probes and
+ * 32 driven nodes, no two of these in one thread's run; and the driven nodes
+ * lie on few planes, so that the step imposes them (lbw_batch_set_sources). */
 int lbw_batch_step_n(lbw_batch_t b, int64_t n);
 
 /* Step count and the device buffer holding the current populations. */

@@ -28,7 +28,8 @@ SYMBOLS = ("lbw_make_geometry", "lbw_make_geometry_general", "lbw_free_geometry"
            "lbw_step_n", "lbw_autotune", "lbw_set_graph_block", "lbw_probe", "lbw_modes", "lbw_modes_noalloc",
            "lbw_state_info",
            "lbw_pressure", "lbw_free_state", "lbw_set_sources", "lbw_amplitude", "lbw_batch_make", "lbw_batch_layout", "lbw_batch_set_step_config",
-           "lbw_batch_get_step_config", "lbw_batch_autotune", "lbw_batch_set_graph_block", "lbw_batch_step_n",
+           "lbw_batch_get_step_config", "lbw_batch_set_steps_per_launch", "lbw_batch_get_steps_per_launch",
+           "lbw_batch_autotune", "lbw_batch_set_graph_block", "lbw_batch_step_n",
            "lbw_batch_info", "lbw_batch_probe", "lbw_batch_modes", "lbw_batch_set_sources",
            "lbw_batch_amplitude", "lbw_batch_free", "lbw_mlp_create",
            "lbw_mlp_param_count", "lbw_mlp_set_params", "lbw_mlp_get_params", "lbw_mlp_forward", "lbw_mlp_loss_grad",
@@ -117,6 +118,8 @@ def lib():
         L.lbw_batch_layout.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(i64)]
         L.lbw_batch_set_step_config.argtypes = [vp, i32, i32, i32]
         L.lbw_batch_get_step_config.argtypes = [vp, ip, ip, ip]
+        L.lbw_batch_set_steps_per_launch.argtypes = [vp, i32]
+        L.lbw_batch_get_steps_per_launch.argtypes = [vp, ip, ip]
         L.lbw_batch_autotune.argtypes = [vp, i32, ctypes.POINTER(ctypes.c_double)]
         L.lbw_batch_set_graph_block.argtypes = [vp, i32]
         L.lbw_batch_step_n.argtypes = [vp, i64]
@@ -410,6 +413,16 @@ class Batch:
         a, b, c = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
         check(lib().lbw_batch_get_step_config(self.handle, ctypes.byref(a), ctypes.byref(b), ctypes.byref(c)))
         return a.value, b.value, c.value
+
+    def set_steps_per_launch(self, steps: int):
+        """1, 2 or 32 (at most); raises where the batch does not fit."""
+        check(lib().lbw_batch_set_steps_per_launch(self.handle, int(steps)))
+
+    def steps_per_launch(self):
+        """(steps, planes per thread): the launches in use."""
+        a, b = ctypes.c_int(), ctypes.c_int()
+        check(lib().lbw_batch_get_steps_per_launch(self.handle, ctypes.byref(a), ctypes.byref(b)))
+        return a.value, b.value
 
     def autotune(self, reps: int = 10) -> float:
         """Times the batch's launch shapes on scratch buffers (state, step

@@ -32,7 +32,7 @@ struct lbw_batch {
     int run = 0, run_threads = 0;
     bool resident = false;
     // two steps per launch: the segments that each workgroup marches (built
-    // and switched on by the tuner)
+    // by the tuner, or where these launches are asked for)
     bool two = false;
     lbw::BatchSegment* d_seg = nullptr;
     int32_t* d_seg_begin = nullptr;  // first segment of each workgroup, blocks2 + 1 entries
@@ -269,22 +269,26 @@ hipError_t build_segments(lbw_batch* b, int cus, bool* ok) {
             if (count > lbw::march2_tile_probes()) return hipSuccess;
         }
     }
-    hipError_t e = hipStreamSynchronize(b->stream);
-    if (e != hipSuccess) return e;
+    // the new tables take the place of the old ones when they are complete
+    lbw::BatchSegment* d_seg = nullptr;
+    int32_t* d_begin = nullptr;
+    hipError_t e = hipMalloc((void**)&d_seg, sizeof(lbw::BatchSegment) * seg.size());
+    if (e == hipSuccess) e = hipMalloc((void**)&d_begin, sizeof(int32_t) * first.size());
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(d_seg, seg.data(), sizeof(lbw::BatchSegment) * seg.size(), hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(d_begin, first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice, b->stream);
+    // (the host tables go out of scope, and queued launches read the old ones)
+    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    if (e != hipSuccess) {
+        (void)hipFree(d_seg);
+        (void)hipFree(d_begin);
+        return e;
+    }
     (void)hipFree(b->d_seg);
     (void)hipFree(b->d_seg_begin);
-    b->d_seg = nullptr;
-    b->d_seg_begin = nullptr;
-    e = hipMalloc((void**)&b->d_seg, sizeof(lbw::BatchSegment) * seg.size());
-    if (e == hipSuccess) e = hipMalloc((void**)&b->d_seg_begin, sizeof(int32_t) * first.size());
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(b->d_seg, seg.data(), sizeof(lbw::BatchSegment) * seg.size(), hipMemcpyHostToDevice,
-                           b->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(b->d_seg_begin, first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice,
-                           b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);  // host tables go out of scope
-    if (e != hipSuccess) return e;
+    b->d_seg = d_seg;
+    b->d_seg_begin = d_begin;
     b->blocks2 = blocks;
     b->threads2 = threads;
     *ok = true;
@@ -625,6 +629,36 @@ int lbw_batch_get_step_config(lbw_batch_t b, int* tile_x, int* chunk_z, int* blo
     if (tile_x) *tile_x = b->tx;
     if (chunk_z) *chunk_z = b->lz;
     if (blocks) *blocks = b->blocks;
+    return LBW_OK;
+}
+
+int lbw_batch_set_steps_per_launch(lbw_batch_t b, int steps) {
+    if (!b) return fail(LBW_EINVAL, "batch is NULL");
+    if (steps != 1 && steps != 2 && steps != lbw::kResidentSteps)
+        return fail(LBW_EINVAL, "steps per launch must be 1, 2 or %d", lbw::kResidentSteps);
+    if (steps == 2) {
+        int cus = 0;
+        const int rc = lbw::device_cus(&cus);
+        if (rc) return rc;
+        bool ok = false;
+        HIP_TRY(build_segments(b, cus, &ok), "lbw_batch_set_steps_per_launch");
+        if (!ok)
+            return fail(LBW_EINVAL, "two steps per launch need walls on axis 0, 4 <= n0 <= 96, no driven nodes and at "
+                                    "most %d probes per segment", lbw::march2_tile_probes());
+    }
+    if (steps == lbw::kResidentSteps && b->run == 0)
+        return fail(LBW_EINVAL, "a geometry, its probes or its driven nodes do not fit one workgroup");
+    b->two = steps == 2;
+    b->resident = steps == lbw::kResidentSteps;
+    b->plan_version += 1;
+    return LBW_OK;
+}
+
+int lbw_batch_get_steps_per_launch(lbw_batch_t b, int* steps, int* planes) {
+    if (!b) return fail(LBW_EINVAL, "batch is NULL");
+    const bool many = b->resident && b->run > 0;
+    if (steps) *steps = many ? lbw::kResidentSteps : two_steps(b) ? 2 : 1;
+    if (planes) *planes = many ? b->run : 0;
     return LBW_OK;
 }
 
