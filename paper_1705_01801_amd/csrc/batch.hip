@@ -727,6 +727,7 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
     if (err == hipSuccess) err = hipEventCreate(&e1);
     const lbw::BatchProbeArgs bp = probe_args(b, false);
     const int keep_tx = b->tx, keep_lz = b->lz, keep_blocks = b->blocks;
+    const bool keep_nts = b->nts;
     int best_tx = keep_tx, best_lz = keep_lz, best_blocks = keep_blocks;
     float best_ms = 1e30f;
     float* other = b->f[1 - b->cur];
@@ -778,7 +779,6 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
         else best_ms = ms;
     }
     // two steps per launch against the best single step
-    b->two = false;
     bool two = false;
     if (err == hipSuccess) err = build_segments(b, cus, &two);
     if (err == hipSuccess && two) {
@@ -826,6 +826,8 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
     if (e1) (void)hipEventDestroy(e1);
     (void)hipStreamSynchronize(b->stream);
     (void)hipFree(tmp);
+    // (after an error the launches that were in use stay so)
+    if (err != hipSuccess) b->nts = keep_nts;
     if (err == hipSuccess) rc = set_config(b, best_tx, best_lz, best_blocks);
     else rc = set_config(b, keep_tx, keep_lz, keep_blocks);
     if (err != hipSuccess) return hip_fail(err, "lbw_batch_autotune");
