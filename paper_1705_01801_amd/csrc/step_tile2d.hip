@@ -14,7 +14,10 @@
 //    values per lane through LDS, and one barrier, per step;
 //  - a probe node's populations are put aside in LDS and summed and divided
 //    by sqrt(g) in FP64 by the whole workgroup when there are many (done by
-//    the owning wave at every step, the division held up all the others);
+//    the owning wave at every step, the division held up all the others).
+//    Each lane knows its own probe nodes, as one bit a row: with every wave
+//    going through the list of places at every step, 64 probes on 64 x 64 nodes
+//    took 6.8 us a step, so 2.4 (1.2 without probes);
 //  - a node next to the tile's outer edge has no neighbour there; what it
 //    computes is wrong, and the error moves in by two nodes per step, so after
 //    k steps exactly the halo is spoilt, which is not written;
@@ -89,12 +92,15 @@ struct Tile2Lds {
     // f*_3 (for the wave above)
     float down[2][3][kMaxWaves][kLanes];
     float up[2][2][kMaxWaves][kLanes];
-    // probes: trace column, wave << 16 | row << 8 | lane, sqrt(g); and the
-    // populations of up to kHeld recordings
+    // probes: trace column, thread << 3 | row, sqrt(g)
     int probe[kTileProbes], place[kTileProbes];
     double sqrtg[kTileProbes];
+    // the rows of a thread that hold probe nodes, the number of its first; and
+    // the populations of up to kHeld recordings of a node
+    unsigned mask[kLanes * kMaxWaves];
+    int base[kLanes * kMaxWaves];
     float held[kHeld][5];
-    int count;
+    int count, nodes;
 };
 
 // FREE: a wall may be a free one (its rule returns the node's own
@@ -160,7 +166,8 @@ __global__ __launch_bounds__(kLanes* kMaxWaves) void step_tile2_kernel(GeomDev g
 
     // the tile's probes
     const int64_t t = *pr.tin;
-    if (threadIdx.x == 0) L.count = 0;
+    L.mask[threadIdx.x] = 0;
+    if (threadIdx.x == 0) L.count = L.nodes = 0;
     __syncthreads();
     if (t >= 0 && t < pr.t_max)
         for (int p = threadIdx.x; p < pr.n; p += blockDim.x) {
@@ -169,10 +176,11 @@ __global__ __launch_bounds__(kLanes* kMaxWaves) void step_tile2_kernel(GeomDev g
             if (i0 < sx.a || i0 >= sx.b || i1 < sy.a || i1 >= sy.b) continue;
             const int slot = atomicAdd(&L.count, 1);
             if (slot < kTileProbes) {
-                const int row = i1 - sy.lo;
+                const int row = i1 - sy.lo, who = row / R * kLanes + i0 - sx.lo;
                 L.probe[slot] = p;
-                L.place[slot] = (row / R) << 16 | (row % R) << 8 | (i0 - sx.lo);
+                L.place[slot] = who << 3 | row % R;
                 L.sqrtg[slot] = g.sqrtg[i0];
+                atomicOr(&L.mask[who], 1u << (row % R));
             }
         }
 
@@ -186,12 +194,21 @@ __global__ __launch_bounds__(kLanes* kMaxWaves) void step_tile2_kernel(GeomDev g
     }
     __syncthreads();
     const int probes = __builtin_amdgcn_readfirstlane(min(L.count, kTileProbes));
-    // the first few probes' places in scalar registers (a place read from LDS
-    // at every step delays every wave)
-    constexpr int kFirst = 4;
-    int first[kFirst];
+    const unsigned mask = L.mask[threadIdx.x];
+    unsigned wave_mask = 0;  // (uniform) rows of the strip with a probe node
+    int base = 0, nodes = 0;
+    if (probes > 0) {
+        if (mask) {
+            base = atomicAdd(&L.nodes, __popc(mask));
+            L.base[threadIdx.x] = base;
+        }
 #pragma unroll
-    for (int i = 0; i < kFirst; ++i) first[i] = i < probes ? __builtin_amdgcn_readfirstlane(L.place[i]) : -1;
+        for (int r = 0; r < R; ++r)
+            if (__builtin_amdgcn_ballot_w64((mask >> r) & 1u)) wave_mask |= 1u << r;
+        __syncthreads();
+        nodes = __builtin_amdgcn_readfirstlane(L.nodes);
+        wave_mask = (unsigned)__builtin_amdgcn_readfirstlane((int)wave_mask);
+    }
     float Sb = L.up[1][0][below][lane], St = L.down[1][0][above][lane];
 
     // One step of the strip: collision and streaming, up to what the
@@ -244,10 +261,11 @@ __global__ __launch_bounds__(kLanes* kMaxWaves) void step_tile2_kernel(GeomDev g
         const int64_t most = pr.t_max - (t + s0);
         const int rows = (int)min((int64_t)(s - s0), most < 0 ? 0 : most);
         for (int i = threadIdx.x; i < rows * probes; i += blockDim.x) {
-            const int p = i % probes;
+            const int p = i % probes, who = L.place[p] >> 3, row = L.place[p] & 7;
+            const int at = i / probes * nodes + L.base[who] + __popc(L.mask[who] & ((1u << row) - 1u));
             double sum = 0.0;
 #pragma unroll
-            for (int l = 0; l < 5; ++l) sum += (double)L.held[i][l];
+            for (int l = 0; l < 5; ++l) sum += (double)L.held[at][l];
             pr.trace[(t + s0 + i / probes) * pr.n + L.probe[p]] = sum / L.sqrtg[p];
         }
         s0 = s;
@@ -255,23 +273,30 @@ __global__ __launch_bounds__(kLanes* kMaxWaves) void step_tile2_kernel(GeomDev g
 
     for (int s = 0; s < steps; ++s) {
         if (probes > 0) {
-            if ((s - s0 + 1) * probes > kHeld) {
+            if ((s - s0 + 1) * nodes > kHeld) {
                 // (the last step's barrier made its recordings visible)
                 flush(s);
                 __syncthreads();
             }
-            const auto put = [&](int i, int place) {
-                if (place >> 16 != wave) return;
-                const int row = (place >> 8) & 255;
+            // (a loop over the strip's probe rows: unrolled, with a branch for
+            // each row, R = 8 takes 45 registers more than there are)
+            if (wave_mask) {
+                const int at = (s - s0) * nodes + base;
+                for (unsigned w = wave_mask; w; w &= w - 1) {
+                    const int row = __builtin_ctz(w);
+                    float v[5];
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (r == row && lane == (place & 255))
+                    for (int l = 0; l < 5; ++l) v[l] = f[0][l];
 #pragma unroll
-                        for (int l = 0; l < 5; ++l) L.held[(s - s0) * probes + i][l] = f[r][l];
-            };
+                    for (int r = 1; r < R; ++r)
+                        if (r == row)
 #pragma unroll
-            for (int i = 0; i < kFirst; ++i) put(i, first[i]);
-            for (int i = kFirst; i < probes; ++i) put(i, __builtin_amdgcn_readfirstlane(L.place[i]));
+                            for (int l = 0; l < 5; ++l) v[l] = f[r][l];
+                    if ((mask >> row) & 1u)
+#pragma unroll
+                        for (int l = 0; l < 5; ++l) L.held[at + __popc(mask & ((1u << row) - 1u))][l] = v[l];
+                }
+            }
         }
         if (nr == R) {
             if (walls0) advance(std::true_type{}, std::true_type{});
