@@ -618,20 +618,24 @@ int lbw_step_n(lbw_state_t s, int64_t n) {
     if (n > 1 && tile2_ok(s)) {
         // a launch of several steps takes longer than queueing the next one,
         // so these are launched directly, not through captured blocks.  The
-        // launches are even or odd in number as the steps are, so that the
         // state ends in the buffer of single steps (an even number of steps
-        // captured by a caller can be replayed); where that takes as many
-        // launches as steps, single steps follow below.
-        const int64_t k = s->g->tile2.k;
-        int64_t launches = (n + k - 1) / k;
-        launches += (launches ^ n) & 1;
+        // captured by a caller can be replayed): a grid that one workgroup
+        // holds goes back to the buffer it came from where it has to, and
+        // launches of tiles are even or odd in number as the steps are.  Where
+        // that takes as many launches as steps, single steps follow below.
+        const lbw::Tile2Plan& p = s->g->tile2;
+        const bool whole = p.ntx * p.nty == 1;
+        int64_t launches = (n + p.k - 1) / p.k;
+        if (!whole) launches += (launches ^ n) & 1;
         if (launches < n) {
             for (; launches > 0; --launches) {
                 const int steps = (int)((n + launches - 1) / launches);
-                HIP_TRY(lbw::launch_step_tile2(s->g->dev, probe_args(s, s->cur), s->g->tile2, steps, s->f[s->cur],
-                                               s->f[1 - s->cur], s->stream),
+                const int to = whole ? s->cur ^ (steps & 1) : 1 - s->cur;
+                lbw::ProbeArgs pr = probe_args(s, s->cur);
+                pr.tout = s->d_tcount + to;
+                HIP_TRY(lbw::launch_step_tile2(s->g->dev, pr, p, steps, s->f[s->cur], s->f[to], s->stream),
                         "lbw_step_n");
-                s->cur ^= 1;
+                s->cur = to;
                 s->t += steps;
                 n -= steps;
             }

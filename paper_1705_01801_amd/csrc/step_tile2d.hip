@@ -103,13 +103,14 @@ struct Tile2Lds {
     int count, nodes;
 };
 
+// fout may be fin, and pr.tout pr.tin, where the grid is one workgroup's.
 // FREE: a wall may be a free one (its rule returns the node's own
 // population; the others scale the outgoing one).
 template <int R, bool FREE>
 __global__ __launch_bounds__(kLanes* kMaxWaves) void step_tile2_kernel(GeomDev g, ProbeArgs pr, Tile2Plan plan,
                                                                        int steps, int share0, int more0, int share1,
-                                                                       int more1, const float* __restrict__ fin,
-                                                                       float* __restrict__ fout) {
+                                                                       int more1, const float* fin,
+                                                                       float* fout) {
 #pragma clang fp contract(off)
     __shared__ Tile2Lds L;
     const int lane = threadIdx.x & 63;
@@ -410,6 +411,7 @@ Tile2Plan make_tile2_plan(const GeomDev& g, int cus) {
 
 hipError_t launch_step_tile2(const GeomDev& g, const ProbeArgs& pr, const Tile2Plan& plan, int steps,
                              const float* fin, float* fout, hipStream_t st) {
+    if (fin == fout && plan.ntx * plan.nty != 1) return hipErrorInvalidValue;
     if (g.dim != 2 || steps < 1 || steps > plan.k || plan.waves < 1 || plan.waves > kMaxWaves) return hipErrorInvalidValue;
     const dim3 grid((unsigned)plan.ntx, (unsigned)plan.nty), block(kLanes * plan.waves);
     bool free = false;
