@@ -732,22 +732,22 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
     float best_ms = 1e30f;
     float* other = b->f[1 - b->cur];
     const int row_nt = section_threads(b);
-    // reps steps of the current configuration on the scratch buffers
-    auto time_current = [&]() -> float {
+    // milliseconds of reps launches on the scratch buffers, after three others:
+    // launch(from, to) queues one
+    auto timed = [&](auto&& launch) -> float {
         float* bufs[2] = {other, tmp};
         int w = 0;
-        if (err == hipSuccess) err = launch_batch(b, bp, b->f[b->cur], other, b->stream);
-        for (int r = 0; r < 2 && err == hipSuccess; ++r, w ^= 1)
-            err = launch_batch(b, bp, bufs[w], bufs[w ^ 1], b->stream);
+        if (err == hipSuccess) err = launch(b->f[b->cur], other);
+        for (int r = 0; r < 2 && err == hipSuccess; ++r, w ^= 1) err = launch(bufs[w], bufs[w ^ 1]);
         if (err == hipSuccess) err = hipEventRecord(e0, b->stream);
-        for (int r = 0; r < reps && err == hipSuccess; ++r, w ^= 1)
-            err = launch_batch(b, bp, bufs[w], bufs[w ^ 1], b->stream);
+        for (int r = 0; r < reps && err == hipSuccess; ++r, w ^= 1) err = launch(bufs[w], bufs[w ^ 1]);
         if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
         if (err == hipSuccess) err = hipEventSynchronize(e1);
         float ms = 0.f;
         if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
         return ms;
     };
+    const auto single = [&](const float* from, float* to) { return launch_batch(b, bp, from, to, b->stream); };
     for (int tx : {0, 16, 32, 64}) {  // 0: whole-row tiles, when every geometry's rows fit them
         if (err != hipSuccess) break;
         if (tx == 0 && row_nt == 0) continue;
@@ -758,7 +758,7 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
                     err = hipErrorUnknown;
                     break;
                 }
-                const float ms = time_current();
+                const float ms = timed(single);
                 if (err != hipSuccess) break;
                 if (ms < best_ms) {
                     best_ms = ms;
@@ -774,7 +774,7 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
     if (err == hipSuccess && set_config(b, best_tx, best_lz, best_blocks) == LBW_OK) {
         const bool policy = b->nts;
         b->nts = !policy;
-        const float ms = time_current();
+        const float ms = timed(single);
         if (!(err == hipSuccess && ms < best_ms)) b->nts = policy;
         else best_ms = ms;
     }
@@ -782,36 +782,18 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
     bool two = false;
     if (err == hipSuccess) err = build_segments(b, cus, &two);
     if (err == hipSuccess && two) {
-        float* bufs[2] = {other, tmp};
-        int w = 0;
-        err = launch_batch2(b, bp, b->f[b->cur], other, b->stream);
-        if (err == hipSuccess) err = hipEventRecord(e0, b->stream);
-        for (int r = 0; r < reps && err == hipSuccess; ++r, w ^= 1)
-            err = launch_batch2(b, bp, bufs[w], bufs[w ^ 1], b->stream);
-        if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
-        if (err == hipSuccess) err = hipEventSynchronize(e1);
-        float ms = 0.f;
-        if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
-        ms *= 0.5f;
+        const float ms =
+            0.5f * timed([&](const float* from, float* to) { return launch_batch2(b, bp, from, to, b->stream); });
         two = err == hipSuccess && ms < best_ms;
         if (two) best_ms = ms;
     }
     // many steps per launch against the best of these
     bool resident = false;
     if (err == hipSuccess && b->run > 0) {
-        lbw::BatchProbeArgs rp = bp;
-        const auto launch = [&] {
-            return lbw::launch_step_resident(b->d_items, b->n, b->run, b->run_threads, b->pery, rp,
-                                             lbw::kResidentSteps, b->f[b->cur], other, b->stream);
-        };
-        err = launch();
-        if (err == hipSuccess) err = hipEventRecord(e0, b->stream);
-        for (int r = 0; r < reps && err == hipSuccess; ++r) err = launch();
-        if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
-        if (err == hipSuccess) err = hipEventSynchronize(e1);
-        float ms = 0.f;
-        if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
-        ms /= (float)lbw::kResidentSteps;
+        const float ms = timed([&](const float* from, float* to) {
+            return lbw::launch_step_resident(b->d_items, b->n, b->run, b->run_threads, b->pery, bp,
+                                             lbw::kResidentSteps, from, to, b->stream);
+        }) / (float)lbw::kResidentSteps;
         if (err == hipSuccess && ms < best_ms) {
             best_ms = ms;
             resident = true;
