@@ -382,7 +382,8 @@ int lbw_batch_get_step_config(lbw_batch_t b, int* tile_x, int* chunk_z, int* blo
  * geometries with walls on axis 0, 4 <= n0 <= 96, no driven nodes and at most
  * 16 probes in any of the equal shares of planes that the workgroups march; or
  * 32, at most so many, with every geometry held on chip by a workgroup of its
- * own, for geometries that fit one (lbw_batch_step_n says which).  The results,
+ * own, for geometries that fit one (lbw_batch_step_n says which), from the first
+ * step on.  The results,
  * and the buffer that holds them, do not depend on it.  The getter gives what
  * is in use, and for 32 the planes per thread (else 0).
  * Errors: LBW_EINVAL (another number, a batch it does not fit), LBW_ENOMEM,
@@ -405,7 +406,8 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us);
 int lbw_batch_set_graph_block(lbw_batch_t b, int steps);
 
 /* Queues n steps of every geometry (probes recorded) without waiting.  Where
- * every geometry is small, up to 32 steps are one launch, unless
+ * every geometry is small, up to 32 steps are one launch (single steps where n
+ * or the rest of it is too short for that to be faster), unless
  * lbw_batch_set_step_config asked for a shape of single steps; the results,
  * and the buffer that holds them, are the same.  Small: with one number R of
  * planes, 2 to 16, for all geometries of the batch, each needs at most 768

@@ -29,7 +29,8 @@ struct lbw_batch {
     int plan_version = 0;
     // several steps per launch, a geometry per workgroup: planes per thread
     // (0: some geometry does not fit) and threads; used where `resident` is set
-    int run = 0, run_threads = 0;
+    // for blocks of at least `run_steps` steps
+    int run = 0, run_threads = 0, run_steps = 1;
     bool resident = false;
     // two steps per launch: the segments that each workgroup marches (built
     // by the tuner, or where these launches are asked for)
@@ -298,7 +299,17 @@ hipError_t build_segments(lbw_batch* b, int cus, bool* ok) {
 // Planes per thread with which every geometry fits a workgroup of the
 // many-step kernel (the fewest: the most threads), and no thread drives two
 // nodes; driven: (geometry, node) of the driven nodes, sorted by geometry.
+// Many steps per launch are taken wherever the geometries fit: from 0.9 against
+// 9.8 us per step (one box of 8 x 8 x 8) to 15 against 79 (476 pipes of 20 x 5 x
+// 100).  A launch loads, lays out its tables for and stores a geometry on one
+// CU, so a single step pays only with short runs: 1, 32 and 256 pipes of 8 x 12 x
+// 96 (12 planes) 13.0, 14.3 and 27.6 us a call against 16.5, 18.3 and 37.9; 119
+// of 16 x 24 x 27 (14) 24.2 against 22.7, of 20 x 5 x 100 (15) 27.5 against 23.2,
+// of 16 x 24 x 31 (16) 28.2 against 23.0; two steps are faster in all of them
+// (35.4 against 46.6 at most).  The tuner, whose single steps are faster, times
+// where the line lies.
 void choose_run(lbw_batch* b, const std::vector<std::pair<int, int64_t>>& driven) {
+    const int before = b->run;
     b->run = 0;
     for (int run = 2; run <= lbw::kResidentRun && b->run == 0; ++run) {
         bool ok = b->n_entries == 0;
@@ -324,6 +335,7 @@ void choose_run(lbw_batch* b, const std::vector<std::pair<int, int64_t>>& driven
         if (ok) {
             b->run = run;
             b->run_threads = threads;
+            if (run != before) b->run_steps = run <= 12 ? 1 : 2;
         }
     }
 }
@@ -588,10 +600,6 @@ int lbw_batch_make(const lbw_geometry_desc* descs, int n, const double* p0, floa
         if (nt > 0 && lane_slots(b, 0) < best) tx = 0;
         const int bpc = tx == 0 ? lbw::batch_section_blocks_per_cu(nt) : lbw::batch_blocks_per_cu(tx);
         if (rc == LBW_OK) rc = set_config(b, tx, 16, (tx == 0 ? 1 : 2) * cus * bpc);
-        // many steps per launch wherever the geometries fit: from 0.9 against
-        // 9.8 us per step (one box of 8 x 8 x 8) to 15 against 79 (476 pipes
-        // of 20 x 5 x 100), and no slower than the tuned single step in any
-        // batch measured (closest: one pipe of 10,000 nodes, 6.7 against 7.6)
         choose_run(b, {});
         b->resident = b->run > 0;
     }
@@ -650,6 +658,7 @@ int lbw_batch_set_steps_per_launch(lbw_batch_t b, int steps) {
         return fail(LBW_EINVAL, "a geometry, its probes or its driven nodes do not fit one workgroup");
     b->two = steps == 2;
     b->resident = steps == lbw::kResidentSteps;
+    b->run_steps = 1;
     b->plan_version += 1;
     return LBW_OK;
 }
@@ -676,9 +685,10 @@ int lbw_batch_step_n(lbw_batch_t b, int64_t n) {
     if (n < 0) return fail(LBW_EINVAL, "negative step count");
     if (b->resident && b->run > 0) {
         // the state goes to the buffer that single steps would leave it in
-        // (an even number of steps: the one it came from)
+        // (an even number of steps: the one it came from); fewer steps than
+        // pay for such a launch follow below
         lbw::BatchProbeArgs bp = probe_args(b, true);
-        while (n > 0) {
+        while (n >= b->run_steps && n > 0) {
             const int k = (int)std::min<int64_t>(n, lbw::kResidentSteps);
             bp.parity = b->cur;
             HIP_TRY(lbw::launch_step_resident(b->d_items, b->n, b->run, b->run_threads, b->pery, bp, k, b->f[b->cur],
@@ -688,7 +698,6 @@ int lbw_batch_step_n(lbw_batch_t b, int64_t n) {
             b->t += k;
             n -= k;
         }
-        return LBW_OK;
     }
     const int K = b->graph_block;
     if (K > 0 && n >= K) {
@@ -779,6 +788,7 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
         else best_ms = ms;
     }
     // two steps per launch against the best single step
+    const float one_ms = best_ms;
     bool two = false;
     if (err == hipSuccess) err = build_segments(b, cus, &two);
     if (err == hipSuccess && two) {
@@ -787,20 +797,31 @@ int lbw_batch_autotune(lbw_batch_t b, int reps, double* best_us) {
         two = err == hipSuccess && ms < best_ms;
         if (two) best_ms = ms;
     }
-    // many steps per launch against the best of these
+    // many steps per launch against the best of these, from the number of steps
+    // on at which they are faster: launches of s steps by the times of 1 and 32
     bool resident = false;
+    int run_steps = 1;
     if (err == hipSuccess && b->run > 0) {
-        const float ms = timed([&](const float* from, float* to) {
-            return lbw::launch_step_resident(b->d_items, b->n, b->run, b->run_threads, b->pery, bp,
-                                             lbw::kResidentSteps, from, to, b->stream);
-        }) / (float)lbw::kResidentSteps;
-        if (err == hipSuccess && ms < best_ms) {
-            best_ms = ms;
+        float ms[2];
+        for (int i = 0; i < 2; ++i)
+            ms[i] = timed([&](const float* from, float* to) {
+                return lbw::launch_step_resident(b->d_items, b->n, b->run, b->run_threads, b->pery, bp,
+                                                 i ? lbw::kResidentSteps : 1, from, to, b->stream);
+            });
+        const float slope = (ms[1] - ms[0]) / (float)(lbw::kResidentSteps - 1);
+        for (int s = 1; s < lbw::kResidentSteps; ++s) {
+            const float others = two ? (float)(s / 4 * 4) * best_ms + (float)(s % 4) * one_ms : (float)s * one_ms;
+            if (ms[0] + (float)(s - 1) * slope > others) run_steps = s + 1;
+        }
+        ms[1] /= (float)lbw::kResidentSteps;
+        if (err == hipSuccess && ms[1] < best_ms) {
+            best_ms = ms[1];
             resident = true;
         }
     }
     if (err == hipSuccess) {
         b->resident = resident;
+        b->run_steps = run_steps;
         b->two = two;
         b->plan_version += 1;
     }
