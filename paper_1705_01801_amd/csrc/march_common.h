@@ -103,18 +103,22 @@ __device__ inline void bload7p(__amdgpu_buffer_rsrc_t r, uint32_t N4, bool on, u
 // = sum_l f_l(node_p) / sqrt(g)), and the step counter advanced by `steps`.
 // The values do not wait for t: a probe costs the node list, then the
 // populations and sqrt(g) together (one workgroup's serial chain was most of
-// a small grid's launch).
+// a small grid's launch); beyond the last trace row only the first of them are
+// read for nothing.
 template <int Q>
 __device__ inline void record_probes(const GeomDev& g, const ProbeArgs& pr, int steps, const float* __restrict__ fin) {
     const int64_t t = *pr.tin;
+    uint32_t next = (int)threadIdx.x < pr.n ? (uint32_t)pr.nodes[threadIdx.x] : 0u;
     for (int p = threadIdx.x; p < pr.n; p += blockDim.x) {
-        const uint32_t node = (uint32_t)pr.nodes[p], N = (uint32_t)g.N;
+        const uint32_t node = next, N = (uint32_t)g.N;
+        if (p + (int)blockDim.x < pr.n) next = (uint32_t)pr.nodes[p + blockDim.x];
         const uint32_t n0 = (uint32_t)g.n0;
         const double sg = g.sqrtg[g.sg_node ? node : node % n0 + n0 * (node / (n0 * (uint32_t)g.n1))];
         double s = 0.0;
 #pragma unroll
         for (int l = 0; l < Q; ++l) s += (double)fin[(uint32_t)l * N + node];
-        if (t >= 0 && t < pr.t_max) pr.trace[t * pr.n + p] = s / sg;
+        if (t < 0 || t >= pr.t_max) break;
+        pr.trace[t * pr.n + p] = s / sg;
     }
     if (threadIdx.x == 0) *pr.tout = t + steps;
 }
