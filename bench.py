@@ -36,7 +36,9 @@ _MARCH2 = ("step_march2.hip", "march_common.h", "lbw_internal.h")
 TRAFFIC = {(1, 1): ("traffic_step_cylinder_128x128x256.txt", _MARCH),
            (2, 1): ("traffic_step_horn_128x128x512.txt", _MARCH),
            (3, 1): ("traffic_step_torus_96x256x512.txt", _MARCH),
-           (4, 1): ("traffic_step_general_duct_128x128x128.txt", ("step_general.hip", "lbw_internal.h")),
+           (4, 1): ("traffic_step_general_duct_128x128x128.txt", ("step_general.hip", "march_common.h",
+                                                                  "lbw_internal.h")),
+           (1, 2): ("traffic_step2_cylinder_128x128x256.txt", _MARCH2),
            (2, 2): ("traffic_step2_horn_128x128x512.txt", _MARCH2),
            (3, 2): ("traffic_step2_torus_96x256x512.txt", _MARCH2)}
 

@@ -473,7 +473,7 @@ int lbw_mlp_param_count(lbw_mlp_t m, int64_t* count);
 /* Copies host FP32 parameters in (and resets the Adam state) / out.  Synchronises. */
 int lbw_mlp_set_params(lbw_mlp_t m, const float* host_params);
 int lbw_mlp_get_params(lbw_mlp_t m, float* host_params);
-/* y[B, widths[L]] = network(x[B, widths[0]]) (device, FP32). */
+/* y[B, widths[L]] = network(x[B, widths[0]]) (device, FP32; the two may overlap). */
 int lbw_mlp_forward(lbw_mlp_t m, const float* x, int B, float* y);
 /* Loss sum_ij w_ij (y_ij - t_ij)^2 / weight_sum (w may be NULL: all 1) and
  * its gradient with respect to the FP32 parameters, kept for

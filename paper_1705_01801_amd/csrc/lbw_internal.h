@@ -74,7 +74,8 @@ struct ProbeArgs {
     int64_t t_max;
     // device step counter in two banks, one per population buffer: a launch
     // reads the bank of the buffer it reads and writes that of the buffer it
-    // writes, so no block of it reads a counter that another block changes
+    // writes, so no block of it reads a counter that another block changes (a
+    // launch of one block may go back to its buffer and bank)
     const int64_t* tin;
     int64_t* tout;
 };
@@ -88,6 +89,7 @@ struct Tile2Plan {
 };
 Tile2Plan make_tile2_plan(const GeomDev& g, int cus);
 int tile2_probes();  // probes a tile records at most
+// fout may be fin where the plan has one tile.
 hipError_t launch_step_tile2(const GeomDev& g, const ProbeArgs& pr, const Tile2Plan& plan, int steps,
                              const float* fin, float* fout, hipStream_t st);
 // One step of a geometry given by its metric (3-D, per-node coefficients),
@@ -123,7 +125,8 @@ hipError_t launch_step_march(const GeomDev& g, const ProbeArgs& pr, const MarchP
 // threads own ty whole axis-0 rows (n0 <= tx, axis 0 walled) over chunks of
 // lz planes, or (lz 0) over balanced shares of all (row tile, plane) pairs;
 // plan.ntx is 1.  Shapes: 96 x 6 and 128 x 4 (768 threads).
-// The step counter advances by two per launch; the probes of both times are recorded, at most march2_tile_probes() per tile.
+// The step counter advances by two per launch; the probes of both times are
+// recorded, at most march2_tile_probes() per tile.
 bool march2_shape_ok(int tx, int ty);
 // Balanced two-step plans (lz 0): workgroup b of `blocks` (a multiple of 8)
 // takes the pairs [a, e) of the `total` (row tile, plane) pairs, row tile

@@ -668,7 +668,10 @@ hipError_t launch_step_batch(const BatchItem* items, const int32_t* tile_item, i
 // those beyond it for the rows: whole-row tiles store aligned, and rows of whole
 // 128-byte lines cost 3.5 less per million nodes.
 // Two steps per launch (balanced shares): 4.5, and per plane of the longest
-// share 0.75 + 0.003 n0 (tiles of 96) or 0.65 + 0.003 n0 (128).
+// share 0.75 + 0.003 n0 (tiles of 96) or 0.65 + 0.003 n0 (128).  Whole chunks of
+// the best length are no reason for another rule: torus 96 x 256 x 512 107.0
+// against 100.1 us per step, horn 128 x 128 x 512 72.0 against 72.7, cylinder 128 x
+// 128 x 256 33.0 against 33.5.
 // The constants are fits to sweeps of every shape over 15 grids.  Measured
 // (32 or 64 wide tiles and chunks of 16, as before, in brackets): horn 24 x 48 x
 // 128 6.1 us (17.1), torus 37 x 61 x 113 8.2 (18.1), box 30 x 200 x 512 36.6

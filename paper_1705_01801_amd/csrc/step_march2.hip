@@ -29,12 +29,19 @@
 //    steps, bit for bit;
 //  - probes: block 0 records time t from the input; the thread that owns a
 //    probe node records time t+1 from the state it assembled.
-// What bounds it: the latency of one plane (about 4900 cycles for 12 waves),
-// of which the vector unit is busy 28 %, the LDS 23 %; memory runs at 3.6 TB/s.
+// What bounds it: on a 96 x 256 x 512 torus a launch moves 1135 MB in 203 us
+// (45.1 bytes per update; 28 if nothing were read twice), 5.6 TB/s, more than a
+// copy of the same bytes reaches, while a plane (about 4900 cycles for 12 waves)
+// keeps the vector unit busy 28 % and the LDS 23 % of its time.  The extra bytes
+// are the price of equal shares, whose neighbours do not march in step: whole
+// chunks move 31 bytes per update, but the best of them (103 planes) takes 107 us
+// per step against 100.
 // Offsets in memory are a lane constant plus a uniform part, and the walls of
 // axis 0 lane constants: 112 vector instructions per plane and wave instead of
-// 178, 100 us per step of a 96 x 256 x 512 torus instead of 104.  Loads two
-// planes ahead did not fit the registers (spills, 110 us).
+// 178, 100 us per step instead of 104.  Loads of the own column and the ring two
+// planes ahead did not fit the registers (spills, 110 us); as built the variants
+// take 137 to 150 of the 168 that three waves per SIMD have, and spill 70 to 114
+// scalar registers to lanes (the batch's: 165 to 167, and 34 to 49).
 // Chunks along axis 2 are extended by two planes of step A either side (the
 // state at t+1 of planes z0-1 and z1 is needed), which is the price of the
 // chunking besides the two halo rows.

@@ -27,12 +27,16 @@
 //    that share a column along axis 1 read the same record, and the LDS serves
 //    equal addresses in one pass only for reads of 4 bytes: with 8-byte reads
 //    of the same table a step took 19.6 us, with these 7.0.
-// 119 driven pipes of 20 x 5 x 100: 7.0 us per step against 19.4 (tuned) with
+// 119 driven pipes of 20 x 5 x 100: 7.5 us per step against 20.8 (tuned) with
 // a launch per step, whose 67 MB a step pass through the caches; 476 of them
-// 14.6 against 73.1.  What bounds it is the one CU that a geometry has: half
+// 15.4 against 75.  What bounds it is the one CU that a geometry has: half
 // of the time its vector units (43 instructions per plane and wave), most of
 // it its LDS (16).  768 threads with up to 16 planes each hold more than 1024
-// with 10, whose registers do not suffice (128 a thread).
+// with 10, whose registers do not suffice (128 a thread).  Up to 12 planes fit
+// the 168 registers that 768 threads leave a lane; from 13 on part of the state is
+// in scratch, 8 to 52 bytes a lane at 13 and 14 planes, 52 and 92 (axis 1 walled)
+// at 15, 96 and 116 at 16, which still pays: walled pipes of 15 and 16 planes take
+// 7.1 and 7.6 us per step against 20.7 and 21.7.
 #include "march_common.h"
 
 namespace lbw {

@@ -28,11 +28,12 @@
 // wall rules and streaming move the same values, so results are those of
 // single steps bit for bit.
 //
-// The vector instructions (about 45 per node, halo included) bound a grid
-// that fits whole, and a third of a tiled one, whose launch, first loads and
-// last stores are the rest.  64 x 64 nodes: 3.95 us a step with one step per
-// launch, 1.40 so (one workgroup, no launches in between); 701 x 503: 10.4
-// and 2.8 (234 tiles of 64 x 64 nodes, six steps per launch).
+// The vector instructions (272 for eight rows with walls on axis 0, 210 without,
+// of which 188 are arithmetic) bound a grid that fits whole, and a third of a
+// tiled one, whose launch, first loads and last stores are the rest.  64 x 64
+// nodes: 3.9 us a step with one step per launch, 1.25 so, 1.27 with a probe (one
+// workgroup, no launches in between); 701 x 503: 10.4 and 2.8 to 3.15 (234 tiles
+// of 64 x 64 nodes, five or six steps per launch).
 #include <type_traits>
 
 #include "march_common.h"
@@ -355,7 +356,9 @@ int tile2_probes() { return kTileProbes; }
 // The constants are from sweeps of rows, strips and k on 64 x 64 and 701 x
 // 503 nodes, which the model meets within 12 %: 701 x 503 in 4 x 16 rows 3.58
 // us a step at k = 4, 3.06 at 5, 2.82 at 6 (7 needs a second round of
-// workgroups); 64 x 64 whole 1.40, in 8 tiles of 24 rows and k = 4 1.71.
+// workgroups); 64 x 64 whole 1.40, in 8 tiles of 24 rows and k = 4 1.71.  On
+// other sizes it gives, and long blocks take: 30 x 40 1.01 and 0.97 us a step, 60
+// x 128 1.37 and 1.39, 150 x 300 1.68 and 1.57, 1600 x 1600 12.9 and 12.2.
 Tile2Plan make_tile2_plan(const GeomDev& g, int cus) {
     constexpr double kLaunch = 4.5, kStep = 0.3, kRow = 0.0186;  // microseconds
     constexpr double kBytes = 5e6;                               // bytes per microsecond
