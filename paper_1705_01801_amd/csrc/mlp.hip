@@ -258,8 +258,6 @@ __device__ __forceinline__ void lds_barrier() {
 constexpr int kFewLayers = 8;
 constexpr int kFewWidth = 256;
 constexpr int kRowWaves = 16;              // waves of rows_kernel, one 16-column tile each
-constexpr int kLdw = kFewWidth + 8;        // LDS row of activations (padded: rows 4 banks apart)
-constexpr int kFragSteps = kFewWidth / 32;
 
 // Offsets of layer l: off parameters (W then b), fwd / bwd the two BF16
 // weight copies, xt its transposed input [w_l][Bp], dzt the transposed
@@ -322,8 +320,14 @@ __device__ inline void schedule_step(const Schedule& s) {
 // that leaves CUs idle is better spread over them so.  TRAIN: t, w, inv as in Gemm; xt and dzt receive what
 // weights_kernel sums, partial[b] the block's share of the loss.  Else y
 // receives the outputs.
-template <bool TRAIN, int RV, int MT>
-__global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __bf16* __restrict__ wf,
+// W: waves, of 16 columns each.  Four or eight serve networks of at most 64 or
+// 128 units and leave room for several workgroups on a CU, where a batch beyond
+// one round of workgroups would otherwise wait for sixteen waves of which few
+// have a tile.  400,000 rows, sixteen waves and so: 3-10 110 and 27 us, 3-32-10
+// 140 and 36, 128-128-128 363 and 209; one layer alone in half the rows again,
+// 72-72 195 and 74.
+template <bool TRAIN, int RV, int MT, int W = kRowWaves>
+__global__ __launch_bounds__(64 * W) void rows_kernel(Net net, const __bf16* __restrict__ wf,
                                                               const float* __restrict__ par,
                                                               const float* __restrict__ x, int B,
                                                               float* __restrict__ y, const float* __restrict__ t,
@@ -333,13 +337,15 @@ __global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __b
     // activations and gradients of every layer when training, else the
     // activations of two
     constexpr int ROWS = RV * MT, J = RV / 4;  // J: values of a lane in a tile
+    constexpr int kWide = 16 * W, kLdw = kWide + 8;  // columns, and the LDS row (padded: rows 4 banks apart)
+    constexpr int kFragSteps = kWide / 32;
     static_assert(RV == 16 || MT == 1, "one tile of repeated rows");
     __shared__ __align__(16) __bf16 act[TRAIN ? kFewLayers : 2][ROWS][kLdw];
     __shared__ __align__(16) __bf16 grad[TRAIN ? kFewLayers : 1][TRAIN ? ROWS : 1][kLdw];
-    __shared__ float red[kRowWaves];
+    __shared__ float red[W];
     __shared__ Net nets;
     __shared__ int4 desc[2 * kFewLayers + 1];
-    __shared__ float biases[kFewLayers][kFewWidth];
+    __shared__ float biases[kFewLayers][kWide];
     const int lane = threadIdx.x & 63, r = lane & 15, grp = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int b0 = blockIdx.x * ROWS;
@@ -380,8 +386,8 @@ __global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __b
                             out, con);
     }
     // all biases
-    for (int i = threadIdx.x; i < L * kFewWidth; i += 64 * kRowWaves) {
-        const int l = i / kFewWidth, n = i % kFewWidth, N = nets.w[l + 1];
+    for (int i = threadIdx.x; i < L * kWide; i += 64 * W) {
+        const int l = i / kWide, n = i % kWide, N = nets.w[l + 1];
         if (n < N) biases[l][n] = par[nets.off[l] + (int64_t)N * nets.w[l] + n];
     }
     lds_barrier();
@@ -401,7 +407,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __b
         const auto block = [&](int s) {
             o.fr[s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, at, s * tiles * 1024, 0));
         };
-        if (o.steps > 2) {
+        if (kFragSteps > 2 && o.steps > 2) {
 #pragma unroll
             for (int s = 0; s < kFragSteps; ++s) block(s);
         } else if (o.steps > 0) {
@@ -412,12 +418,19 @@ __global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __b
     Operand o;
     load(o, 0);
     const int k0 = __builtin_amdgcn_readfirstlane(nets.w[0]);
-    for (int i = threadIdx.x; i < ROWS * kFewWidth; i += 64 * kRowWaves) {
-        const int m = i / kFewWidth, k = i % kFewWidth;
-        const bool ok = b0 + m < B && k < k0;
-        const float v = x[ok ? (int64_t)(b0 + m) * k0 + k : 0];
-        act[0][m][k] = ok ? (__bf16)v : (__bf16)0.0f;
-    }
+    // (the first product reads the columns of two steps, or all)
+    const auto inputs = [&](auto columns) {
+        constexpr int C = decltype(columns)::value;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < ROWS * C; i += 64 * W) {
+            const int m = i / C, k = i % C;
+            const bool ok = b0 + m < B && k < k0;
+            const float v = x[ok ? (int64_t)(b0 + m) * k0 + k : 0];
+            act[0][m][k] = ok ? (__bf16)v : (__bf16)0.0f;
+        }
+    };
+    if (k0 <= 64) inputs(std::integral_constant<int, 64>{});
+    else inputs(std::integral_constant<int, kWide>{});
     // this lane's column, and the loss's targets and weights there
     const int n = wave * 16 + r;
     float tv[MT][J], wv[MT][J];
@@ -448,7 +461,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __b
                 acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, o.fr[s], acc[m], 0, 0, 0);
             }
         };
-        if (o.steps > 2) {
+        if (kFragSteps > 2 && o.steps > 2) {
 #pragma unroll
             for (int s = 0; s < kFragSteps; ++s) step(s);
         } else if (o.steps > 0) {
@@ -504,7 +517,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __b
         // everything transposed: ROWS batch values of a column at a time
         typedef __bf16 bf16xr __attribute__((ext_vector_type(ROWS)));
         for (int l = 0; l < L; ++l)
-            for (int i = threadIdx.x; i < nets.w[l] + nets.w[l + 1]; i += 64 * kRowWaves) {
+            for (int i = threadIdx.x; i < nets.w[l] + nets.w[l + 1]; i += 64 * W) {
                 const bool x_part = i < nets.w[l];
                 const int c = x_part ? i : i - nets.w[l];
                 bf16xr q;
@@ -517,7 +530,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void rows_kernel(Net net, const __b
         lds_barrier();
         if (threadIdx.x == 0) {
             float s = 0.f;
-            for (int i = 0; i < kRowWaves; ++i) s += red[i];
+            for (int i = 0; i < W; ++i) s += red[i];
             partial[blockIdx.x] = s;
         }
     }
@@ -781,7 +794,7 @@ struct lbw_mlp {
     // activations and gradients of a training step (offsets for batch Bp),
     // and the rate and bias corrections of the step
     bool few = false;
-    int cus = 256;
+    int cus = 256, widest = 0;
     Net net{};
     __bf16* wf = nullptr;
     int64_t wf_size = 0;
@@ -894,10 +907,13 @@ Net net_for(const lbw_mlp* M, int B) {
 
 // Outputs y of B rows of x, one launch: as many rows per workgroup, 4 to 64,
 // as give each CU one workgroup (each reads all the weights, and a second
-// round of workgroups costs as much as the first).
-template <int RV, int MT>
+// round of workgroups costs as much as the first).  Beyond that, workgroups of as
+// few waves as the widest layer needs, of 64 rows, or 32 where a single layer of
+// up to 128 units leaves mostly memory to wait for (8-128, 400,000 rows: 55 us
+// against 67).
+template <int RV, int MT, int W = kRowWaves>
 void launch_rows(lbw_mlp* M, const float* x, int B, float* y) {
-    hipLaunchKernelGGL((rows_kernel<false, RV, MT>), dim3((B + RV * MT - 1) / (RV * MT)), dim3(64 * kRowWaves), 0,
+    hipLaunchKernelGGL((rows_kernel<false, RV, MT, W>), dim3((B + RV * MT - 1) / (RV * MT)), dim3(64 * W), 0,
                        M->stream, M->net, M->wf, M->p, x, B, y, nullptr, nullptr, 0.f, 0, nullptr, nullptr,
                        Schedule{});
 }
@@ -908,6 +924,9 @@ hipError_t few_forward(lbw_mlp* M, const float* x, int B, float* y) {
     else if (B <= 16 * cus) launch_rows<16, 1>(M, x, B, y);
     else if (B <= 32 * cus) launch_rows<16, 2>(M, x, B, y);
     else if (B <= 48 * cus) launch_rows<16, 3>(M, x, B, y);
+    else if (M->widest <= 64) launch_rows<16, 4, 4>(M, x, B, y);
+    else if (M->widest <= 128 && M->L == 1) launch_rows<16, 2, 8>(M, x, B, y);
+    else if (M->widest <= 128) launch_rows<16, 4, 8>(M, x, B, y);
     else launch_rows<16, 4>(M, x, B, y);
     return hipGetLastError();
 }
@@ -964,6 +983,7 @@ int lbw_mlp_create(const int32_t* widths, int n_layers, int max_batch, void* str
         if (M->w[l] > maxw) maxw = M->w[l];
     }
     M->P = P;
+    M->widest = (int)maxw;
     const int64_t bw = (int64_t)max_batch * maxw;
     // (the last bound: offsets of rows x width elements stay within 32 bits)
     M->few = n_layers <= kFewLayers && maxw <= kFewWidth && max_batch <= (1 << 22);
