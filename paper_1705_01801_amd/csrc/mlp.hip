@@ -26,8 +26,8 @@
 // weights are loaded while a layer's epilogue runs.  Both issue the products
 // of gemm_kernel below in its order, so the results are the same bits.
 // (The loss, a sum of FP32 shares, is added up in another order.)
-// Forward of 10,000 rows, 3-256-256-256-10: 74 us with a launch per layer, 14.5
-// so, of which the tanh of 7.7 million activations is about 12.  A training
+// Forward of 10,000 rows, 3-256-256-256-10: 74 us with a launch per layer, 13.6
+// so, most of it the tanh of 7.7 million activations.  A training
 // step of 512 rows: 72 us in nine launches; 17 + 10 us in two.  rows_kernel is
 // bound by each CU reading every weight (0.85 us per 256 x 256 layer at 64
 // bytes a cycle) and by the chain of layers, weights_kernel by a trip to
